@@ -102,7 +102,8 @@ __global__ void k_build_tables(LevelWalk W, const double4* __restrict__ dirs, Di
         }
         while (px < nx_) idx[D.ix + (uint32_t)(++px - D.px0)] = (uint32_t)n;
         while (pz < nz_) idx[D.iz + (uint32_t)(++pz - D.pz0)] = (uint32_t)n;
-        segs[D.off + n] = Segment{(sz * nz_ * W.nx + sx * nx_) * (int)(tab::kLB * 8), (float)len};
+        // (entries that lie outside the domain for every probe may wrap: no ray reads them)
+        segs[D.off + n] = Segment{(int)(uint32_t)(((int64_t)(sz * nz_) * W.nx + sx * nx_) * (tab::kLB * 8)), (float)len};
         ++n;
     };
     if (T0 < T1) {
@@ -267,6 +268,10 @@ hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vec
         W.tb = L.tb;
         W.dmax_x = std::max((L.px - 0.5) * L.s, g.nx - 0.5 * L.s);
         W.dmax_z = std::max((L.pz - 0.5) * L.s, g.nz - 0.5 * L.s);
+        // furthest cell from a probe's own that a ray inside the domain crosses
+        // (the last probes of a ragged grid lie past its far edge)
+        const double far_x = std::max((L.px - 1) * L.s + std::floor(0.5 * L.s), g.nx - 1.0);
+        const double far_z = std::max((L.pz - 1) * L.s + std::floor(0.5 * L.s), g.nz - 1.0);
         const int32_t nc = W.fix ? tab::kFixClasses : 1;
         dt.resize(first[i] + (size_t)L.nd * nc);
         first[i + 1] = dt.size();
@@ -274,6 +279,12 @@ hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vec
         for (int32_t k = 0; k < L.nd * nc; ++k) {
             const Line d = list_line(W, dirs[dir_off[i] + k / nc], k % nc);
             const double len = std::max(d.t1 - d.t0, 0.0), wx = std::fabs(d.x), wz = std::fabs(d.z);
+            // keys are 32-bit byte offsets with sign: where a ray can cross a
+            // cell 2^24 cells away (within a few percent of the largest grids,
+            // with probes past the edge) the plan walks
+            const double reach = std::min(std::fabs(d.oz + d.z * d.t1) + 2.0, far_z) * g.nx +
+                                 std::min(std::fabs(d.ox + d.x * d.t1) + 2.0, far_x);
+            if (len > 0.0 && reach * (tab::kLB * 8) >= 2147483648.0) return hipSuccess;
             DirTable& D = dt[first[i] + k];
             D.cap = (int32_t)(len * (wx + wz)) + 8;
             D.off = (uint32_t)n_seg;

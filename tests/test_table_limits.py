@@ -1,0 +1,37 @@
+"""Which plans march from segment tables, and that their 32-bit offsets hold
+every place they reach (host code, on a stand-in for the HIP runtime)."""
+import pytest
+
+from host_runtime import run
+
+
+@pytest.mark.parametrize("nx,nz", [
+    (4096, 4096),   # offsets up to 2^24 - 1 cells
+    (4095, 4097),   # cascade 6: a probe in row 4128 reaches row 0, 4128 x 4095 > 2^24 cells
+    (65280, 257),
+    (257, 65280),
+    (4000, 4000),
+])
+def test_segment_keys_hold_every_offset(tmp_path, nx, nz):
+    """A segment's key is the byte offset, at 128 B a cell, from its probe's
+    cell to the cell crossed, in 32 bits with sign. Probes of a ragged grid
+    lie past its far edge, so the offset can pass 2^24 cells on a grid that
+    holds fewer: such plans walk, the others keep their tables."""
+    far = 0
+    for i in range(10):
+        s = 1 << i
+        if i and 1.5 * 4 ** (i - 1) >= ((nx + s) ** 2 + (nz + s) ** 2) ** 0.5:
+            continue  # every ray starts outside the domain
+        x0 = (-(-nx // s) - 1) * s + s // 2
+        z0 = (-(-nz // s) - 1) * s + s // 2
+        far = max(far, max(z0, nz - 1) * nx + max(x0, nx - 1))
+    tables = far * 128 < 2**31
+    assert tables == ((nx, nz) in [(4096, 4096), (257, 65280), (4000, 4000)])
+    run(tmp_path, f"""
+        p = plan({nx}, {nz})
+        built = count(launches(), "k_build_tables")
+        ls = solve(p, {nx}, {nz})
+        assert (built > 0) == {tables}, built
+        assert (count(ls, "k_march_table") > 0) == {tables}
+        assert (count(ls, "k_march_rows") > 0) == (not {tables})
+    """)
