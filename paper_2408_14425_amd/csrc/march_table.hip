@@ -258,6 +258,10 @@ hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vec
         const LevelDesc& L = levels[i];
         // 32-bit byte offsets of the fields, probe cells past a ragged edge included
         if (((double)L.pz * L.s + 1.0) * g.nx * tab::kLB * 8 >= 4294967296.0) return hipSuccess;
+        // 32-bit places in a stored cascade of 16 wavelengths (every direction's
+        // code, or the means of 4): long, narrow grids with wide cascades walk
+        const double stored = (double)L.px * L.pz * L.nd / (prm.storage == RCX_STORE_F16_SCALED ? 1 : 4);
+        if (i > 0 && stored * tab::kLB >= 4294967296.0) return hipSuccess;
         LevelWalk& W = lw[i];
         W.nd = L.nd;
         W.odd = L.s == 1.0;

@@ -35,3 +35,23 @@ def test_segment_keys_hold_every_offset(tmp_path, nx, nz):
         assert (count(ls, "k_march_table") > 0) == {tables}
         assert (count(ls, "k_march_rows") > 0) == (not {tables})
     """)
+
+
+@pytest.mark.parametrize("nx,nz,n_cascades,f16", [
+    (8, 140000, 10, False), (8, 140000, 10, True), (8, 131072, 10, True), (8, 120000, 10, True), (333, 200, 0, True)])
+def test_cascade_places_fit_32_bits(tmp_path, nx, nz, n_cascades, f16):
+    """The march's places in a stored cascade (16 wavelengths of every
+    direction's 16-bit code, or of the FP32 means of 4) are 32-bit: a plan with
+    a cascade of more walks. On 8 x 140000 the cascade of spacing 512 holds 274
+    probes x 2^20 directions."""
+    n = n_cascades or 7
+    most = max(-(-nx // 2**i) * -(-nz // 2**i) * 4 ** (i + 1) * 16 // (1 if f16 else 4) for i in range(1, n))
+    tables = most < 2**32
+    assert tables == ((nx, nz, f16) not in [(8, 140000, True), (8, 131072, True)])
+    run(tmp_path, f"""
+        p = plan({nx}, {nz}, storage={int(f16)}, n_cascades={n_cascades})
+        assert (count(launches(), "k_build_tables") > 0) == {tables}
+        ls = solve(p, {nx}, {nz})
+        assert (count(ls, "k_march_table") > 0) == {tables}
+        assert (count(ls, "k_march_rows") > 0) == (not {tables})
+    """)
