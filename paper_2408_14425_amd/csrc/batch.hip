@@ -52,7 +52,7 @@ struct rcx_batch {
         uint32_t blocks;
         bool j;
     };
-    std::vector<Step> steps;   // one launch per cascade, top first
+    std::vector<Step> steps;   // a launch per cascade (more where its grid would be too large), top first
     std::vector<float*> J_bound;
     int64_t n_march = 0;       // march launches the last solve enqueued
     // graph
@@ -86,23 +86,37 @@ int32_t build_tasks(rcx_batch* s)
         s->kind[a] = plan_table_tasks(P, s->n_wave[a], s->J_bound[a], by[a]) ? 2 : 1;
         if (s->kind[a] == 2) top = std::max(top, P->n_casc);
     }
-    std::vector<char> host;
+    std::vector<char> host(bytes);
+    auto task = [&](int32_t a, int32_t i, uint32_t block0, char* at) {
+        const rcx_plan* P = s->plans[a];
+        return table_task(P->levels[i], P->tables[i], P->grid.nx, P->grid.nz, by[a][i], block0, at);
+    };
+    // (a cascade that no launch holds)
+    for (int32_t a = 0; a < s->n_atm; ++a)
+        for (int32_t i = 0; s->kind[a] == 2 && i < s->plans[a]->n_casc; ++i)
+            if (by[a][i].out && task(a, i, 0, host.data()) > kMaxGridX) s->kind[a] = 1;
+    host.clear();
     s->steps.clear();
     for (int32_t i = top - 1; i >= 0; --i) {
-        rcx_batch::Step step{(int32_t)(host.size() / bytes), 0, 0, i == 0};
-        uint64_t blocks = 0;
+        rcx_batch::Step step{0, 0, 0, i == 0};
         for (int32_t a = 0; a < s->n_atm; ++a) {
-            const rcx_plan* P = s->plans[a];
-            if (s->kind[a] != 2 || i >= P->n_casc || !by[a][i].out) continue;
+            if (s->kind[a] != 2 || i >= s->plans[a]->n_casc || !by[a][i].out) continue;
             host.resize(host.size() + bytes);
-            const uint64_t n = table_task(P->levels[i], P->tables[i], P->grid.nx, P->grid.nz, by[a][i],
-                                          (uint32_t)blocks, host.data() + host.size() - bytes);
-            if (n == 0) host.resize(host.size() - bytes);  // sparse with nothing flagged
-            else ++step.n;
-            blocks += n;
+            char* at = host.data() + host.size() - bytes;
+            uint64_t n = task(a, i, step.blocks, at);
+            if (step.blocks + n > kMaxGridX) {  // the launch is full: the next one starts here
+                s->steps.push_back(step);
+                step.n = 0;
+                step.blocks = 0;
+                n = task(a, i, 0, at);
+            }
+            if (n == 0) {  // sparse with nothing flagged
+                host.resize(host.size() - bytes);
+                continue;
+            }
+            if (step.n++ == 0) step.t0 = (int32_t)(host.size() / bytes) - 1;
+            step.blocks += (uint32_t)n;
         }
-        if (blocks >= (1ull << 31)) return bfail(RCX_E_UNSUPPORTED, "rcx_batch_solve: too many workgroups");
-        step.blocks = (uint32_t)blocks;
         if (step.n > 0) s->steps.push_back(step);
     }
     if (host.size() > s->tasks_cap) {

@@ -267,13 +267,13 @@ extern "C" int32_t rcx_emergent(rcx_plan* p, int32_t n_wave, const float* chi, c
     const double4 d = make_double4(dx, dz, 1.0 / dx, 1.0 / dz);
     // the pieces' {I, T} lie in the plan's own workspace, which holds 128 B per
     // cell and 16 wavelengths of max_wave at least, so one ray of every
-    // wavelength and piece; a beam too wide for it (hundreds of domain widths)
-    // goes in slices
+    // wavelength and piece; a beam too wide for it (hundreds of domain widths),
+    // or for a launch's grid, goes in slices
     const bool xmaj = std::fabs(d.x) >= std::fabs(d.y);
     const int32_t pieces = ((xmaj ? nx : nz) - 1) / kTile + 1;
     const int64_t room = (int64_t)(p->ws_own_bytes / sizeof(float2)) / ((int64_t)pieces * n_wave);
     const int32_t slice =
-        (int32_t)std::min({(int64_t)n_rays, room, std::max<int64_t>((int64_t(1) << 30) / pieces, 1) * kRays});
+        (int32_t)std::min({(int64_t)n_rays, room, (int64_t)(kMaxGridX / (uint32_t)pieces) * kRays});
     Beam B{ox0, oz0, -wz, wx, d, n_rays, 0, 0};
     for (B.r0 = 0; B.r0 < n_rays; B.r0 = B.r1) {
         B.r1 = (int32_t)std::min<int64_t>((int64_t)B.r0 + slice, n_rays);

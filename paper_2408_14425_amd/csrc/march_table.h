@@ -65,6 +65,7 @@ struct Work {
     uint32_t sub, cone_final;  // cone * 2 + final
 };
 constexpr int kSegPad = 8;  // entries readable past a list's end
+static_assert(kMaxGridX % march::kXcds == 0, "launches start on the first XCD");
 
 struct LaunchArgs {
     // geometry
@@ -76,6 +77,7 @@ struct LaunchArgs {
     // launch order: workgroup -> (tile, wedge of cones) group, then cone
     // (fastest), then the sub-block of probes a wavefront takes
     uint32_t n_blocks;
+    uint32_t block0 = 0;     // this launch's first workgroup (kMaxGridX at a time)
     FastDiv per, nwedge, wd, nb_long, ntx, chunk, chunk8;
     int32_t tile_x, tile_z;  // probes of a tile
     int32_t tw_log2, th;     // sub-block: 2^tw_log2 x th probes, x th <-> z on z-long sub-blocks
@@ -660,7 +662,7 @@ __device__ __forceinline__ uint32_t place(const LaunchArgs& A, uint32_t b)
 template <int LB, int W, int OUT, bool UPF16, bool WIN, bool FIX = false>
 __global__ __launch_bounds__(kBlock, W == 1 ? 8 : 4) void k_march_table(LaunchArgs A, Slots<W> sl)
 {
-    uint32_t lb = blockIdx.x;
+    uint32_t lb = A.block0 + blockIdx.x;
     if constexpr (WIN) {
         // XCD x takes the x-th eighth of the window's list (sorted by region)
         lb = (lb % march::kXcds) * A.chunk.d + lb / march::kXcds;
@@ -753,7 +755,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_march_fix_table(LaunchArgs A)
     __shared__ float red[4][V][64];
     const int lane = threadIdx.x & 63, l = (lane & (LPR - 1)) * V, row = lane / LPR;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    uint32_t lb = place(A, blockIdx.x);
+    uint32_t lb = place(A, A.block0 + blockIdx.x);
     if (lb >= A.n_blocks) return;
     const uint32_t batch = blockIdx.y;
     const int pu = (int)(lb & 1u), pv = (int)((lb >> 1) & 1u);

@@ -454,17 +454,31 @@ uint64_t set_order(tab::LaunchArgs& A, const LevelDesc& L)
     return blocks;
 }
 
+// Workgroups [0, blocks) of a march in launches of at most kMaxGridX:
+// go(grid.x) with A.block0 set.
+template <class Go>
+hipError_t launch_blocks(tab::LaunchArgs& A, uint64_t blocks, Go&& go)
+{
+    if (blocks >= (1ull << 32) - march::kXcds) return hipErrorInvalidValue;
+    const uint64_t all = (blocks + march::kXcds - 1) / march::kXcds * march::kXcds;
+    for (uint64_t b = 0; b < all; b += kMaxGridX) {
+        A.block0 = (uint32_t)b;
+        go((unsigned)std::min<uint64_t>(all - b, kMaxGridX));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <int LB, int W, int OUT, bool UPF16>
 hipError_t launch_k(tab::LaunchArgs& A, const LevelDesc& L, int32_t n_batch, const tab::Slots<W>& sl, hipStream_t st)
 {
     set_plain<LB, W, OUT>(A, L);
     const uint64_t blocks = set_order<LB, W, OUT>(A, L);
-    if (blocks == 0) return hipSuccess;
-    if (blocks >= (1ull << 31) - 8) return hipErrorInvalidValue;
-    const unsigned gx = (unsigned)((blocks + march::kXcds - 1) / march::kXcds * march::kXcds);
-    hipLaunchKernelGGL((tab::k_march_table<LB, W, OUT, UPF16, false>), dim3(gx, (unsigned)n_batch), dim3(march::kBlock), 0, st,
-                       A, sl);
-    return hipGetLastError();
+    return launch_blocks(A, blocks, [&](unsigned gx) {
+        hipLaunchKernelGGL((tab::k_march_table<LB, W, OUT, UPF16, false>), dim3(gx, (unsigned)n_batch),
+                           dim3(march::kBlock), 0, st, A, sl);
+    });
 }
 
 template <int LB>
@@ -503,14 +517,15 @@ hipError_t launch_windows(tab::LaunchArgs& A, const LevelTable& T, int32_t n_bat
         A.tap = (int32_t)(w / per_tap);
         const uint32_t per_xcd = (A.n_blocks + march::kXcds - 1) / march::kXcds;
         A.chunk = make_fastdiv(per_xcd);
-        const dim3 grid(per_xcd * march::kXcds, (unsigned)n_batch);
-        if (OUT == tab::kOutMean && fix)
-            hipLaunchKernelGGL((tab::k_march_table<tab::kLB, 1, tab::kOutMean, false, true, true>), grid,
-                               dim3(march::kBlock), 0, st, A, sl);
-        else
-            hipLaunchKernelGGL((tab::k_march_table<tab::kLB, 1, OUT, UPF16, true>), grid, dim3(march::kBlock), 0, st, A,
-                               sl);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch_blocks(A, A.n_blocks, [&](unsigned gx) {
+            const dim3 grid(gx, (unsigned)n_batch);
+            if (OUT == tab::kOutMean && fix)
+                hipLaunchKernelGGL((tab::k_march_table<tab::kLB, 1, tab::kOutMean, false, true, true>), grid,
+                                   dim3(march::kBlock), 0, st, A, sl);
+            else
+                hipLaunchKernelGGL((tab::k_march_table<tab::kLB, 1, OUT, UPF16, true>), grid, dim3(march::kBlock), 0,
+                                   st, A, sl);
+        });
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -557,14 +572,14 @@ hipError_t launch_fix(tab::LaunchArgs& A, LevelDesc L, const TableLaunch& io, hi
     L.tile_p = (L.tile_p + 1) / 2;
     L.xcd_chunk *= 4;
     const uint64_t blocks = 4 * set_order<LB, 1, tab::kOutMean>(A, L);
-    if (blocks >= (1ull << 31) - 8) return hipErrorInvalidValue;
     A.n_blocks = (uint32_t)blocks;
-    const dim3 grid((unsigned)((blocks + march::kXcds - 1) / march::kXcds * march::kXcds), (unsigned)io.n_batch);
-    if (io.J)
-        hipLaunchKernelGGL((tab::k_march_fix_table<LB, tab::kOutJ>), grid, dim3(march::kBlock), 0, st, A);
-    else
-        hipLaunchKernelGGL((tab::k_march_fix_table<LB, tab::kOutMean>), grid, dim3(march::kBlock), 0, st, A);
-    return hipGetLastError();
+    return launch_blocks(A, blocks, [&](unsigned gx) {
+        const dim3 grid(gx, (unsigned)io.n_batch);
+        if (io.J)
+            hipLaunchKernelGGL((tab::k_march_fix_table<LB, tab::kOutJ>), grid, dim3(march::kBlock), 0, st, A);
+        else
+            hipLaunchKernelGGL((tab::k_march_fix_table<LB, tab::kOutMean>), grid, dim3(march::kBlock), 0, st, A);
+    });
 }
 }  // namespace
 
@@ -632,7 +647,10 @@ hipError_t launch_two(tab::LaunchArgs& A, tab::LaunchArgs& B, const LevelDesc& L
     set_plain<LB, 1, OUT>(B, L);
     const uint64_t a = up8(set_order<tab::kLB, 1, OUT>(A, L)), b = up8(set_order<LB, 1, OUT>(B, L));
     if (a == 0) return hipSuccess;  // (nothing flagged)
-    if (a * n_batch + b >= (1ull << 31)) return hipErrorInvalidValue;
+    if (a * n_batch + b > kMaxGridX) {
+        const hipError_t e = launch_k<tab::kLB, 1, OUT, UPF16>(A, L, n_batch, tab::Slots<1>{}, st);
+        return e != hipSuccess ? e : launch_k<LB, 1, OUT, UPF16>(B, L, 1, tab::Slots<1>{}, st);
+    }
     hipLaunchKernelGGL((tab::k_march_two<LB, OUT, UPF16>), dim3((unsigned)(a * n_batch + b)), dim3(march::kBlock), 0, st,
                        A, B, (uint32_t)b, make_fastdiv((uint32_t)a));
     return hipGetLastError();

@@ -402,8 +402,14 @@ mlpf::Net fused_net(const rcx_mlp* s)
 
 hipError_t fused_forward(rcx_mlp* s, const float* x, float* y, int32_t B, hipStream_t st)
 {
-    hipLaunchKernelGGL(mlpf::k_forward, dim3(nblk(B, mlpf::kFwdTile)), dim3(256), 0, st, fused_net(s), x, y, (int64_t)B);
-    return hipGetLastError();
+    constexpr int32_t kMost = 1 << 30;  // samples of a launch (a grid's limit)
+    for (int32_t b0 = 0;; b0 += kMost) {
+        const int32_t n = std::min(B - b0, kMost);
+        hipLaunchKernelGGL(mlpf::k_forward, dim3(nblk(n, mlpf::kFwdTile)), dim3(256), 0, st, fused_net(s),
+                           x + (int64_t)b0 * s->n_in, y + (int64_t)b0 * s->n_out, (int64_t)n);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || n == B - b0) return e;
+    }
 }
 
 // Workgroups of the fused gradients: two tiles of 32 samples each up to the

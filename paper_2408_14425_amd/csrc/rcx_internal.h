@@ -35,6 +35,10 @@ inline FastDiv make_fastdiv(uint32_t d)
     return f;
 }
 
+// Workgroups of 256 of a launch along x: a grid holds less than 2^32 work items
+// along an axis.
+constexpr uint32_t kMaxGridX = (1u << 24) - 8;
+
 constexpr uint32_t kDecodeReady = 0x52435844u;
 
 // Geometry of one cascade as the march/merge kernel sees it.
@@ -205,7 +209,8 @@ hipError_t launch_march_table2(const LevelDesc& L, const LevelTable& T, int32_t 
 // The same cascade of several atmospheres (16 lanes, flatland) in one launch:
 // table_task writes one task (table_task_bytes) whose workgroups start at
 // block0 and returns their number; launch_table_tasks runs n tasks of
-// `blocks` workgroups in all, every one with J (cascade 0) or none.
+// `blocks` workgroups in all (at most kMaxGridX), every one with J (cascade 0)
+// or none.
 size_t table_task_bytes();
 uint64_t table_task(const LevelDesc& L, const LevelTable& T, int32_t nx, int32_t nz, const TableLaunch& io,
                     uint32_t block0, void* task);
