@@ -506,13 +506,33 @@ int32_t solve_batches(rcx_plan* p, int32_t n_wave, float* J, const WsLayout& w, 
 }
 
 
+// The windows of every cascade; one whose lists find no memory is marched whole.
 hipError_t plan_windows(rcx_plan* p)
 {
     hipError_t e = hipSuccess;
     if (p->prm.n_incl != 1 && !p->walk_solves) return e;
     const bool fix = (p->prm.flags & RCX_FLAG_BILINEAR_FIX) != 0;
-    for (int32_t i = 1; i < p->n_casc && e == hipSuccess; ++i)
-        e = build_windows(p->grid, p->levels[i], p->dirs_dev + p->dir_off[i], fix && i + 1 < p->n_casc, p->tables[i]);
+    for (int32_t i = 1; i < p->n_casc; ++i) {
+        const hipError_t r =
+            build_windows(p->grid, p->levels[i], p->dirs_dev + p->dir_off[i], fix && i + 1 < p->n_casc, p->tables[i]);
+        if (r == hipErrorOutOfMemory) (void)hipGetLastError();
+        else if (e == hipSuccess) e = r;
+    }
+    return e;
+}
+
+// Every probe active again.
+hipError_t drop_flags(rcx_plan* p)
+{
+    hipError_t e = hipSuccess;
+    if (p->mask_dev) e = hipFree(p->mask_dev);
+    if (p->plist_dev && e == hipSuccess) e = hipFree(p->plist_dev);
+    p->mask_dev = nullptr;
+    p->plist_dev = nullptr;
+    for (auto& L : p->levels) {
+        L.plist = nullptr;
+        L.n_active = 0;
+    }
     return e;
 }
 
@@ -800,8 +820,7 @@ int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, 
     e = plan_windows(p);
     if (e != hipSuccess) {
         rcx_plan_destroy(p);
-        return e == hipErrorOutOfMemory ? fail(RCX_E_NOMEM, "rcx_plan_create: window lists")
-                                        : hip_fail(e, "rcx_plan_create: window lists");
+        return hip_fail(e, "rcx_plan_create: window lists");
     }
     p->windowed = has_windows(p);  // (workspace sizes do not depend on flags set later)
     p->ws_own_bytes = ws_layout(p, max_wave).total;
@@ -857,16 +876,7 @@ int32_t rcx_plan_set_active_host(rcx_plan* p, const uint8_t* active_host, int64_
         p->active_host.assign(active_host, active_host + (size_t)nx * nz);
     else if (!active_host)
         p->active_host.clear();
-    // drop any previous flags: every probe active
-    hipError_t e = hipSuccess;
-    if (p->mask_dev) e = hipFree(p->mask_dev);
-    if (p->plist_dev && e == hipSuccess) e = hipFree(p->plist_dev);
-    p->mask_dev = nullptr;
-    p->plist_dev = nullptr;
-    for (auto& L : p->levels) {
-        L.plist = nullptr;
-        L.n_active = 0;
-    }
+    hipError_t e = drop_flags(p);
     if (e != hipSuccess) return hip_fail(e, "rcx_plan_set_active_host: hipFree");
     if (!active_host) {
         if (level_active_host)
@@ -925,18 +935,20 @@ int32_t rcx_plan_set_active_host(rcx_plan* p, const uint8_t* active_host, int64_
     if (e == hipSuccess) e = hipMalloc(&p->plist_dev, sizeof(int32_t) * std::max<size_t>(all.size(), 1));
     if (e == hipSuccess && !all.empty())
         e = hipMemcpy(p->plist_dev, all.data(), sizeof(int32_t) * all.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        for (int32_t i = 0; i < p->n_casc; ++i) {
+            p->levels[i].plist = p->plist_dev + off[i];
+            p->levels[i].n_active = cnt[i];
+        }
+        e = plan_windows(p);
+    }
     if (e != hipSuccess) {
-        if (p->mask_dev) (void)hipFree(p->mask_dev);
-        if (p->plist_dev) (void)hipFree(p->plist_dev);
-        p->mask_dev = nullptr;
-        p->plist_dev = nullptr;
+        // dense, and so are the windows
+        (void)hipGetLastError();
+        (void)drop_flags(p);
+        (void)plan_windows(p);
         return hip_fail(e, "rcx_plan_set_active_host");
     }
-    for (int32_t i = 0; i < p->n_casc; ++i) {
-        p->levels[i].plist = p->plist_dev + off[i];
-        p->levels[i].n_active = cnt[i];
-    }
-    RCX_HIP_TRY(plan_windows(p));
     return ok();
 }
 
