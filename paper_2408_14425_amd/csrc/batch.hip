@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <chrono>
 #include <fstream>
+#include <new>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -334,7 +335,12 @@ int32_t rcx_batch_solve(rcx_batch* s, const float* const* chi_host, const float*
         s->J_bound.assign(J_host, J_host + s->n_atm);
         if (s->dirty || !same_J) {
             s->dirty = true;
-            const int32_t rc = build_tasks(s);
+            int32_t rc;
+            try {
+                rc = build_tasks(s);
+            } catch (const std::bad_alloc&) {
+                rc = bfail(RCX_E_NOMEM, "rcx_batch_solve: host allocation");
+            }
             if (rc != RCX_OK) return rc;
         }
     }

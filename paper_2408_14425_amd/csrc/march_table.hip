@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 
 namespace rcx {
 
@@ -235,9 +236,10 @@ size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 
 }  // namespace
 
-hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vector<LevelDesc>& levels,
-                        bool top_skipped, const std::vector<double4>& dirs, const std::vector<int32_t>& dir_off,
-                        const double4* dirs_dev, std::vector<LevelTable>& tables, void** mem)
+namespace {
+hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vector<LevelDesc>& levels,
+                       bool top_skipped, const std::vector<double4>& dirs, const std::vector<int32_t>& dir_off,
+                       const double4* dirs_dev, std::vector<LevelTable>& tables, void** mem)
 {
     const int32_t n_casc = (int32_t)levels.size();
     tables.assign(n_casc, LevelTable{});
@@ -330,6 +332,18 @@ hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vec
         tables.assign(n_casc, LevelTable{});
     }
     return e;
+}
+}  // namespace
+
+hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vector<LevelDesc>& levels,
+                        bool top_skipped, const std::vector<double4>& dirs, const std::vector<int32_t>& dir_off,
+                        const double4* dirs_dev, std::vector<LevelTable>& tables, void** mem)
+{
+    try {
+        return make_tables(g, prm, levels, top_skipped, dirs, dir_off, dirs_dev, tables, mem);
+    } catch (const std::bad_alloc&) {
+        return hipErrorOutOfMemory;
+    }
 }
 
 int32_t table_lanes(int32_t n, int64_t ncell)
@@ -744,7 +758,14 @@ hipError_t build_windows(const rcx_grid& g, const LevelDesc& L, const double4* d
     hipError_t e = hipMalloc(&bins, n_bin * sizeof(uint32_t));
     if (e != hipSuccess) return e;
     const unsigned grid = (G.n_sub * G.n_cone + 255) / 256;
-    std::vector<uint32_t> h(n_bin);
+    std::vector<uint32_t> h;
+    try {
+        h.resize(n_bin);
+        T.win_start.reserve((size_t)taps * G.n_win + 1);
+    } catch (const std::bad_alloc&) {
+        (void)hipFree(bins);
+        return hipErrorOutOfMemory;
+    }
     e = hipMemset(bins, 0, n_bin * sizeof(uint32_t));
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_windows, dim3(grid, taps), dim3(256), 0, nullptr, G, dirs, bins, (tab::Work*)nullptr);

@@ -1486,8 +1486,9 @@ static int32_t line_group(const rcx_nlte* s, int32_t b, int32_t gmax)
     return 1;
 }
 
-int32_t rcx_nlte_create(const rcx_grid* g, const rcx_params* p, const rcx_atom* atom, int32_t n_wave,
-                        const double* lambda_nm_host, const int32_t* trans_host, const double* dnu_host, rcx_nlte** out)
+static int32_t create_solver(const rcx_grid* g, const rcx_params* p, const rcx_atom* atom, int32_t n_wave,
+                             const double* lambda_nm_host, const int32_t* trans_host, const double* dnu_host,
+                             rcx::PlanFor use, rcx_nlte** out)
 {
     if (out) *out = nullptr;
     if (!g || !p || !atom || !lambda_nm_host || !trans_host || !dnu_host || !out)
@@ -1523,7 +1524,7 @@ int32_t rcx_nlte_create(const rcx_grid* g, const rcx_params* p, const rcx_atom* 
 
     rcx_nlte* s = new (std::nothrow) rcx_nlte();
     if (!s) return nlte_fail(RCX_E_NOMEM, "rcx_nlte_create: host allocation");
-    int32_t rc = rcx::plan_create(g, p, kLB, true, &s->plan);
+    int32_t rc = rcx::plan_create(g, p, kLB, use, &s->plan);
     if (rc != RCX_OK) {
         delete s;
         return rc;
@@ -1700,6 +1701,20 @@ int32_t rcx_nlte_create(const rcx_grid* g, const rcx_params* p, const rcx_atom* 
     }
     *out = s;
     return RCX_OK;
+}
+
+int32_t rcx_nlte_create(const rcx_grid* g, const rcx_params* p, const rcx_atom* atom, int32_t n_wave,
+                        const double* lambda_nm_host, const int32_t* trans_host, const double* dnu_host, rcx_nlte** out)
+{
+    // with the plan's segment tables, or without where they leave no memory
+    // for the solver
+    int32_t rc = RCX_OK;
+    for (const rcx::PlanFor use : {rcx::PlanFor::kNlte, rcx::PlanFor::kNlteWalk}) {
+        rc = create_solver(g, p, atom, n_wave, lambda_nm_host, trans_host, dnu_host, use, out);
+        if (rc != RCX_E_NOMEM) break;
+        (void)hipGetLastError();  // (a launch is not to report it again)
+    }
+    return rc;
 }
 
 int32_t rcx_nlte_set_charge_conservation(rcx_nlte* s, int32_t enable)

@@ -302,14 +302,11 @@ struct rcx_plan {
 };
 
 namespace rcx {
-// The formal solve of rcx_formal_solve on the plan's own workspace, enqueue
-// only: no argument or input check and no synchronisation, so a stream
-// capture may record it (the batched path runs its large atmospheres
-// through it). *march_launches (nullable) receives the march launches it
-// enqueued.
-// rcx_plan_create for the non-LTE solver: the plan's own solves walk
-// (rcx_plan::walk_solves).
-int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, bool walk_solves, rcx_plan** out);
+// rcx_plan_create for its own solves, or for the non-LTE solver, which marches
+// the plan's tables itself (rcx_plan::walk_solves) or, where there is no
+// memory for them, walks.
+enum class PlanFor { kSolves, kNlte, kNlteWalk };
+int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, PlanFor use, rcx_plan** out);
 // A small atmosphere of a batch: its field preparation on the plan's own
 // workspace in 16-lane batches (plan_enqueue_prep), and its cascades as tasks
 // (plan_table_tasks: one per marched cascade into tasks[level], empty where
@@ -317,6 +314,11 @@ int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, 
 // its workspace does not hold every batch at once).
 int32_t plan_enqueue_prep(rcx_plan* p, int32_t n_wave, const float* chi, const float* eta, hipStream_t st);
 bool plan_table_tasks(rcx_plan* p, int32_t n_wave, float* J, std::vector<TableLaunch>& by_level);
+// The formal solve of rcx_formal_solve on the plan's own workspace, enqueue
+// only: no argument or input check and no synchronisation, so a stream
+// capture may record it (the batched path runs its large atmospheres
+// through it). *march_launches (nullable) receives the march launches it
+// enqueued.
 int32_t plan_enqueue_solve(rcx_plan* p, int32_t n_wave, const float* chi, const float* eta, float* J,
                            hipStream_t st, int64_t* march_launches);
 }  // namespace rcx

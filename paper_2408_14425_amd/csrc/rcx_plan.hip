@@ -521,6 +521,18 @@ hipError_t plan_windows(rcx_plan* p)
     return e;
 }
 
+// Without tables (and windows) the plan walks.
+void drop_tables(rcx_plan* p)
+{
+    for (auto& T : p->tables) {
+        if (T.work) (void)hipFree(T.work);
+        T = LevelTable{};
+    }
+    if (p->table_mem) (void)hipFree(p->table_mem);
+    p->table_mem = nullptr;
+    p->windowed = false;
+}
+
 // Every probe active again.
 hipError_t drop_flags(rcx_plan* p)
 {
@@ -662,6 +674,8 @@ int32_t enqueue_prep(rcx_plan* p, int32_t n_wave, const float* chi, const float*
     return RCX_OK;
 }
 
+int32_t set_active(rcx_plan* p, const uint8_t* active_host, int64_t* level_active_host);
+
 // The launches of one formal solve (after any input check).
 int32_t enqueue_solve(rcx_plan* p, int32_t n_wave, const float* chi, const float* eta, float* J,
                              const WsLayout& w, char* ws, hipStream_t st)
@@ -704,12 +718,28 @@ int32_t rcx_params_default(rcx_params* p)
 
 int32_t rcx_plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, rcx_plan** out)
 {
-    return plan_create(g, prm, max_wave, false, out);
+    return plan_create(g, prm, max_wave, PlanFor::kSolves, out);
 }
 }  // extern "C"
 
 namespace rcx {
-int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, bool walk_solves, rcx_plan** out)
+static void free_plan(rcx_plan* p)
+{
+    for (auto& t : p->pending) {
+        (void)hipEventDestroy(t.a);
+        (void)hipEventDestroy(t.b);
+    }
+    drop_tables(p);
+    (void)drop_flags(p);
+    if (p->dirs_dev) (void)hipFree(p->dirs_dev);
+    if (p->ws_own) (void)hipFree(p->ws_own);
+    delete p;
+}
+
+static int32_t make_plan(rcx_plan* p, const rcx_grid* g, const rcx_params* prm, int32_t max_wave, int32_t n_casc,
+                         PlanFor use);
+
+int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, PlanFor use, rcx_plan** out)
 {
     if (out) *out = nullptr;
     if (!g || !prm || !out) return fail(RCX_E_INVALID, "rcx_plan_create: null argument");
@@ -735,6 +765,24 @@ int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, 
 
     rcx_plan* p = new (std::nothrow) rcx_plan();
     if (!p) return fail(RCX_E_NOMEM, "rcx_plan_create: host allocation");
+    int32_t rc;
+    try {
+        rc = make_plan(p, g, prm, max_wave, n_casc, use);
+    } catch (const std::bad_alloc&) {
+        rc = fail(RCX_E_NOMEM, "rcx_plan_create: host allocation");
+    }
+    if (rc != RCX_OK) {
+        free_plan(p);
+        (void)hipGetLastError();  // (the next launch is not to report it again)
+        return rc;
+    }
+    *out = p;
+    return ok();
+}
+
+static int32_t make_plan(rcx_plan* p, const rcx_grid* g, const rcx_params* prm, int32_t max_wave, int32_t n_casc,
+                         PlanFor use)
+{
     p->grid = *g;
     p->prm = *prm;
     p->prm.n_cascades = n_casc;
@@ -794,34 +842,26 @@ int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, 
     }
 
     hipError_t e = hipMalloc(&p->dirs_dev, sizeof(double4) * p->dirs_host.size());
-    if (e != hipSuccess) {
-        delete p;
-        return hip_fail(e, "hipMalloc(directions)");
-    }
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc(directions)");
     e = hipMemcpy(p->dirs_dev, p->dirs_host.data(), sizeof(double4) * p->dirs_host.size(),
                   hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        rcx_plan_destroy(p);
-        return hip_fail(e, "hipMemcpy(directions)");
-    }
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy(directions)");
     p->tables.resize(n_casc);
-    p->walk_solves = walk_solves;
+    const bool nlte = use != PlanFor::kSolves;
+    p->walk_solves = nlte;
     // (the fix marches from tables in flatland with FP32 cascades)
-    if (prm->flags & RCX_FLAG_BILINEAR_FIX ? prm->n_incl == 1 && prm->storage == RCX_STORE_F32 && !walk_solves
-                                           : prm->n_incl == 1 || incl_slots(p) || walk_solves) {
+    if (use != PlanFor::kNlteWalk &&
+        (prm->flags & RCX_FLAG_BILINEAR_FIX ? prm->n_incl == 1 && prm->storage == RCX_STORE_F32 && !nlte
+                                            : prm->n_incl == 1 || incl_slots(p) || nlte)) {
         e = build_tables(p->grid, p->prm, p->levels, p->top_skipped != 0, p->dirs_host, p->dir_off, p->dirs_dev,
                          p->tables, &p->table_mem);
         if (e == hipErrorOutOfMemory) (void)hipGetLastError();  // the plan walks
         else if (e != hipSuccess) {
-            rcx_plan_destroy(p);
-            return hip_fail(e, "rcx_plan_create: segment tables");
+                return hip_fail(e, "rcx_plan_create: segment tables");
         }
     }
     e = plan_windows(p);
-    if (e != hipSuccess) {
-        rcx_plan_destroy(p);
-        return hip_fail(e, "rcx_plan_create: window lists");
-    }
+    if (e != hipSuccess) return hip_fail(e, "rcx_plan_create: window lists");
     p->windowed = has_windows(p);  // (workspace sizes do not depend on flags set later)
     p->ws_own_bytes = ws_layout(p, max_wave).total;
     e = hipMalloc(&p->ws_own, p->ws_own_bytes);
@@ -831,19 +871,19 @@ int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, 
         p->ws_own_bytes = ws_layout(p, max_wave, false).total;
         e = hipMalloc(&p->ws_own, p->ws_own_bytes);
     }
+    if (e == hipErrorOutOfMemory && p->table_mem) {
+        // nor for the tables
+        (void)hipGetLastError();
+        drop_tables(p);
+        p->ws_own_bytes = ws_layout(p, max_wave).total;
+        e = hipMalloc(&p->ws_own, p->ws_own_bytes);
+    }
     if (e != hipSuccess) {
         p->ws_own = nullptr;
-        rcx_plan_destroy(p);
         return fail(RCX_E_NOMEM, std::string("rcx_plan_create: workspace hipMalloc: ") + hipGetErrorName(e));
     }
     // the allocation-free solve's scratch on this device (looked up once)
-    const int32_t rc = scratch_address(&p->scratch);
-    if (rc != RCX_OK) {
-        rcx_plan_destroy(p);
-        return rc;
-    }
-    *out = p;
-    return ok();
+    return scratch_address(&p->scratch);
 }
 
 }  // namespace rcx
@@ -870,6 +910,20 @@ int32_t rcx_formal_solve_noalloc(rcx_plan* p, int32_t n_wave, const float* chi, 
 int32_t rcx_plan_set_active_host(rcx_plan* p, const uint8_t* active_host, int64_t* level_active_host)
 {
     if (!p) return fail(RCX_E_INVALID, "rcx_plan_set_active_host: null plan");
+    try {
+        return set_active(p, active_host, level_active_host);
+    } catch (const std::bad_alloc&) {
+        // dense, and so are the windows
+        (void)drop_flags(p);
+        (void)plan_windows(p);
+        return fail(RCX_E_NOMEM, "rcx_plan_set_active_host: host allocation");
+    }
+}
+}  // extern "C"
+
+namespace {
+int32_t set_active(rcx_plan* p, const uint8_t* active_host, int64_t* level_active_host)
+{
     const int32_t nx = p->grid.nx, nz = p->grid.nz;
     // keep the flags: a change of launch order rebuilds the lists from them
     if (active_host && active_host != p->active_host.data())
@@ -951,6 +1005,10 @@ int32_t rcx_plan_set_active_host(rcx_plan* p, const uint8_t* active_host, int64_
     }
     return ok();
 }
+
+}  // namespace
+
+extern "C" {
 
 int32_t rcx_plan_workspace_bytes(const rcx_plan* p, int32_t n_wave, size_t* bytes)
 {
@@ -1187,18 +1245,7 @@ int32_t rcx_autotune(rcx_plan* p, const char* cache_path, hipStream_t st)
 int32_t rcx_plan_destroy(rcx_plan* p)
 {
     if (!p) return ok();
-    for (auto& t : p->pending) {
-        (void)hipEventDestroy(t.a);
-        (void)hipEventDestroy(t.b);
-    }
-    if (p->dirs_dev) (void)hipFree(p->dirs_dev);
-    if (p->ws_own) (void)hipFree(p->ws_own);
-    if (p->table_mem) (void)hipFree(p->table_mem);
-    for (auto& T : p->tables)
-        if (T.work) (void)hipFree(T.work);
-    if (p->mask_dev) (void)hipFree(p->mask_dev);
-    if (p->plist_dev) (void)hipFree(p->plist_dev);
-    delete p;
+    free_plan(p);
     return ok();
 }
 
