@@ -149,12 +149,15 @@ __global__ void k_build_tables(LevelWalk W, const double4* __restrict__ dirs, Di
 // in memory between windows (16 B per window against 8 B per entry).
 constexpr int kWindow = 128;
 constexpr int kRegion = 64;    // cells per side (a workgroup's own segments spread over 100-230)
+// bins of (window, region, wedge) at most, larger regions beyond (4096^2 takes
+// 7e6, 3e7 with the fix; a 64 x 140000 strip would take 8e7 of the 64^2 ones)
+constexpr size_t kMaxBins = size_t(1) << 25;
 constexpr int kDirBins = 32;   // wedges of directions, in order within a region
 
 struct WindowGeom {
     tab::LaunchArgs A;  // geometry, directions, lists, sub-blocks, flagged probes
     uint32_t n_sub, n_cone;
-    int32_t nrx, nrz, n_win;  // n_win: of one tap
+    int32_t region, nrx, nrz, n_win;  // n_win: of one tap
     int32_t fix;              // 4 taps, the sub-blocks of each parity
     double s, ta;
 };
@@ -223,7 +226,7 @@ __global__ void k_windows(WindowGeom G, const double4* __restrict__ dirs, uint32
     const double per = 1.0 / (fabs(d.x) + fabs(d.y));
     for (int w = w0; w < w1; ++w) {
         const double t = G.ta + (w + 0.5) * kWindow * per;
-        const int x = (int)((u + 0.5) * G.s + t * d.x) / kRegion, z = (int)((v + 0.5) * G.s + t * d.y) / kRegion;
+        const int x = (int)((u + 0.5) * G.s + t * d.x) / G.region, z = (int)((v + 0.5) * G.s + t * d.y) / G.region;
         const int rx = min(max(x, 0), G.nrx - 1), rz = min(max(z, 0), G.nrz - 1);
         const uint32_t bin = (uint32_t)(((tap * G.n_win + w) * G.nrz + rz) * G.nrx + rx) * kDirBins +
                              (uint32_t)((uint64_t)cone * kDirBins / G.n_cone);
@@ -293,6 +296,7 @@ hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vect
             if (len > 0.0 && reach * (tab::kLB * 8) >= 2147483648.0) return hipSuccess;
             DirTable& D = dt[first[i] + k];
             D.cap = (int32_t)(len * (wx + wz)) + 8;
+            tables[i].max_entries = std::max(tables[i].max_entries, D.cap);
             D.off = (uint32_t)n_seg;
             D.ix = (uint32_t)n_idx;
             D.iz = D.ix + (uint32_t)(len * wx) + 6;
@@ -744,16 +748,17 @@ hipError_t build_windows(const rcx_grid& g, const LevelDesc& L, const double4* d
                       : std::max(subs(G.A.px, G.A.pz, tab::kWinShort, tab::kWinLong),
                                  subs(G.A.px, G.A.pz, tab::kWinLong, tab::kWinShort)) * taps;  // (fix: 4 parities)
     G.n_cone = (uint32_t)L.nd / 4;
-    G.nrx = (g.nx + kRegion - 1) / kRegion;
-    G.nrz = (g.nz + kRegion - 1) / kRegion;
     G.s = L.s;
     G.ta = L.ta;
-    // entries per list: at most reach x sqrt(2) + the table's slack
-    // (the fix's rays end up to 2.2 spacings past theirs)
-    G.n_win = (int32_t)((std::hypot((double)L.px * L.s, (double)L.pz * L.s) + reach + (fix ? 3.0 * L.s : 0.0)) * 1.5 /
-                        kWindow) + 2;
+    G.n_win = (T.max_entries - 1) / kWindow + 1;
     if ((uint64_t)G.n_sub * G.n_cone >= (1ull << 31)) return hipSuccess;
-    const size_t n_bin = (size_t)taps * G.n_win * G.nrx * G.nrz * kDirBins;
+    size_t n_bin;
+    for (G.region = kRegion;; G.region *= 2) {
+        G.nrx = (g.nx + G.region - 1) / G.region;
+        G.nrz = (g.nz + G.region - 1) / G.region;
+        n_bin = (size_t)taps * G.n_win * G.nrx * G.nrz * kDirBins;
+        if (n_bin <= kMaxBins || G.nrx * G.nrz == 1) break;
+    }
     uint32_t* bins = nullptr;
     hipError_t e = hipMalloc(&bins, n_bin * sizeof(uint32_t));
     if (e != hipSuccess) return e;

@@ -117,6 +117,7 @@ struct LevelTable {
     const void* dirs = nullptr;
     const void* segs = nullptr;
     const uint32_t* idx = nullptr;
+    int32_t max_entries = 0;  // of the longest list, at most
     // windowed march (march_table.hip): the workgroups of window w are
     // work[win_start[w]..win_start[w + 1]) (bilinear fix: 4 taps' windows one
     // after the other); none: the cascade is marched whole

@@ -21,7 +21,8 @@ static struct { const void* fn; char name[512]; } fns[1024];
 static int n_fns;
 static char* log_text;
 static size_t log_len, log_cap;
-static size_t live, largest;
+static size_t live, sizes[256];
+static int n_sizes;
 
 static int set(int e)
 {
@@ -31,14 +32,15 @@ static int set(int e)
 
 void fake_fail_malloc(int n, int m) { fail_at = n; fail_count = m; }
 size_t fake_live_bytes(void) { return live; }
-size_t fake_largest(void) { size_t b = largest; largest = 0; return b; }
+/* sizes of the allocations asked for since the last call */
+int fake_sizes(size_t* out) { int n = n_sizes; memcpy(out, sizes, sizeof(size_t) * (size_t)n); n_sizes = 0; return n; }
 const char* fake_log(void) { return log_text ? log_text : ""; }
 void fake_log_clear(void) { log_len = 0; if (log_text) log_text[0] = 0; }
 
 int hipMalloc(void** p, size_t n)
 {
     *p = NULL;
-    if (n > largest) largest = n;
+    if (n_sizes < 256) sizes[n_sizes++] = n;
     if (fail_count > 0 && fail_at-- <= 0) {
         --fail_count;
         return set(kOutOfMemory);

@@ -19,7 +19,6 @@ import ctypes as C, sys
 rt = C.CDLL({shim!r}, mode=C.RTLD_GLOBAL)
 rt.fake_log.restype = C.c_char_p
 rt.fake_live_bytes.restype = C.c_size_t
-rt.fake_largest.restype = C.c_size_t
 rt.fake_fail_malloc.argtypes = [C.c_int, C.c_int]
 rt.hipMalloc.argtypes = [C.POINTER(C.c_void_p), C.c_size_t]
 sys.path.insert(0, {root!r})
@@ -49,6 +48,10 @@ def launches(clear=True):
     if clear:
         rt.fake_log_clear()
     return out
+
+def mallocs():
+    out = (C.c_size_t * 256)()
+    return list(out[:rt.fake_sizes(out)])
 
 def count(ls, kernel):
     return sum(kernel in l[0] for l in ls)

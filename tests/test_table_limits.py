@@ -55,3 +55,18 @@ def test_cascade_places_fit_32_bits(tmp_path, nx, nz, n_cascades, f16):
         assert (count(ls, "k_march_table") > 0) == {tables}
         assert (count(ls, "k_march_rows") > 0) == (not {tables})
     """)
+
+
+@pytest.mark.parametrize("nx,nz,windowed,most", [(512, 512, 1, 2**17), (64, 140000, 1, 2**27), (1500, 1500, 2, 2**20)])
+def test_window_bins_follow_the_lists(tmp_path, nx, nz, windowed, most):
+    """The bins that sort a windowed cascade's workgroups by (window, region,
+    wedge) are as many as its longest list has windows (the cascade of spacing
+    16 on 512^2: 288 cells x sqrt 2, so 4 windows of 128, on 8 x 8 regions in
+    32 wedges), 2^25 at most."""
+    run(tmp_path, f"""
+        p = plan({nx}, {nz})
+        n = count(launches(), "k_windows") // 2
+        assert n >= {windowed}, n
+        bins = mallocs()[2:2 + 2 * n:2]
+        assert all(b <= {most} for b in bins), bins
+    """)
