@@ -239,6 +239,7 @@ struct rcx_mlp {
     float* P = nullptr;  // weight-gradient partials
     float* loss_part = nullptr;
     float* part = nullptr;  // fused gradients: partial gradients of the workgroups
+    double* sq_part = nullptr;  // and their sums of squared errors
     float* loss_pinned = nullptr;  // fused gradients: the loss, in host memory the device writes
     int64_t t = 0;
     std::vector<void*> allocs;
@@ -428,7 +429,7 @@ hipError_t fused_gradients(rcx_mlp* s, const float* x, const float* yref, int32_
     const int blocks = grad_blocks(B);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(mlpf::kThreads), 0, st, fused_net(s), x, yref, B, s->part,
-                           s->loss_part);
+                           s->sq_part);
     };
     if (s->depth == 1) go(mlpf::k_gradients<1>);
     else if (s->depth == 2) go(mlpf::k_gradients<2>);
@@ -438,7 +439,7 @@ hipError_t fused_gradients(rcx_mlp* s, const float* x, const float* yref, int32_
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mlpf::k_sum_partials, dim3(nblk(s->n_params, mlpf::kSumParams)),
                        dim3(mlpf::kSlices * mlpf::kSumParams), 0, st, s->part, blocks, s->n_in, s->n_out, s->depth,
-                       s->n_params, grad, s->loss_part, 1.0 / ((double)B * s->n_out), s->loss_pinned);
+                       s->n_params, grad, s->sq_part, 1.0 / ((double)B * s->n_out), s->loss_pinned);
     return hipGetLastError();
 }
 
@@ -495,7 +496,7 @@ int32_t rcx_mlp_create(int32_t n_in, int32_t width, int32_t depth, int32_t n_out
     if (fused(s)) {
         const int blocks = grad_blocks(max_batch);
         chk(dalloc(s, &s->part, sizeof(float) * blocks * mlpf::partial_floats(depth)));
-        chk(dalloc(s, &s->loss_part, sizeof(float) * blocks));
+        chk(dalloc(s, &s->sq_part, sizeof(double) * blocks));
         chk(hipHostMalloc((void**)&s->loss_pinned, sizeof(float), hipHostMallocDefault));
     } else {
         s->Hs.resize(s->n_layers);

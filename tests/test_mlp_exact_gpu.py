@@ -42,3 +42,20 @@ def test_silu_where_the_sigmoid_is_tiny(z):
     print(y, yo, gb[0], go[0])
     assert np.abs(y - yo).max() <= 2 * 2.0**-9 * np.abs(yo).max()
     assert np.abs(gb - go).max() <= 5 * 2.0**-9 * np.abs(go).max()
+
+
+@pytest.mark.parametrize("batch", [1000, 1 << 20])
+def test_loss_of_equal_errors(batch):
+    """A network of zeros against a constant: every squared error is the same
+    FP32 number c, so the mean is c, to the rounding of 1 / (batch x outputs)
+    and of the result (2^-23) when the sums are exact or in FP64."""
+    n_out = 4
+    flat = np.zeros(6 * 128 + 128 + 128 * n_out + n_out, np.float32)
+    print(f"[gpu] loss of {batch}", flush=True)
+    net, torch = _net(6, 1, n_out, batch, flat)
+    yr = torch.full((batch, n_out), 1.1, device="cuda", dtype=torch.float32)
+    loss, _ = net.gradients(torch.zeros((batch, 6), device="cuda"), yr)
+    net.close()
+    c = np.float32(1.1) * np.float32(1.1)
+    print(loss, c)
+    assert abs(float(loss) - float(c)) <= 2.0**-23 * float(c)
