@@ -2,6 +2,7 @@
 // the march that reads them (march_table.h; Osborne & Sannikov,
 // arXiv:2408.14425, Secs. 2.2-2.3).
 #include "march_table.h"
+#include "segment_length.h"
 
 #include <algorithm>
 #include <cmath>
@@ -69,8 +70,9 @@ __host__ __device__ inline Line list_line(const LevelWalk& W, double4 d, int32_t
 // in cell (0, 0) on an unbounded grid, with the same FP64 arithmetic, so a
 // ray steps the same segments, in the same order, with the same lengths
 // (with the bilinear fix to FP64 rounding: its rays start at p + t_a w).
+// rest (nullable): what the FP32 lengths leave out.
 __global__ void k_build_tables(LevelWalk W, const double4* __restrict__ dirs, DirTable* __restrict__ dt,
-                               Segment* __restrict__ segs, uint32_t* __restrict__ idx)
+                               Segment* __restrict__ segs, uint32_t* __restrict__ idx, float* __restrict__ rest)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     const int nc = W.fix ? tab::kFixClasses : 1;
@@ -105,6 +107,7 @@ __global__ void k_build_tables(LevelWalk W, const double4* __restrict__ dirs, Di
         while (pz < nz_) idx[D.iz + (uint32_t)(++pz - D.pz0)] = (uint32_t)n;
         // (entries that lie outside the domain for every probe may wrap: no ray reads them)
         segs[D.off + n] = Segment{(int)(uint32_t)(((int64_t)(sz * nz_) * W.nx + sx * nx_) * (tab::kLB * 8)), (float)len};
+        if (rest) rest[D.off + n] = length_rest(len);
         ++n;
     };
     if (T0 < T1) {
@@ -242,7 +245,7 @@ size_t up256(size_t b) { return (b + 255) & ~size_t(255); }
 namespace {
 hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vector<LevelDesc>& levels,
                        bool top_skipped, const std::vector<double4>& dirs, const std::vector<int32_t>& dir_off,
-                       const double4* dirs_dev, std::vector<LevelTable>& tables, void** mem)
+                       const double4* dirs_dev, bool rests, std::vector<LevelTable>& tables, void** mem)
 {
     const int32_t n_casc = (int32_t)levels.size();
     tables.assign(n_casc, LevelTable{});
@@ -250,7 +253,7 @@ hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vect
     if (prm.c0_dirs != 4) return hipSuccess;
     const bool fix = (prm.flags & RCX_FLAG_BILINEAR_FIX) != 0;
     struct Off {
-        size_t dirs, segs, idx;
+        size_t dirs, segs, idx, rest;
     };
     std::vector<Off> off(n_casc);
     std::vector<DirTable> dt;  // every cascade's, copied at once
@@ -308,6 +311,8 @@ hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vect
         total += up256(sizeof(Segment) * (size_t)n_seg);
         off[i].idx = total;
         total += up256(sizeof(uint32_t) * (size_t)n_idx);
+        off[i].rest = total;
+        if (rests) total += up256(sizeof(float) * (size_t)n_seg);
     }
     const size_t dirs_at = total;
     total += up256(sizeof(DirTable) * dt.size());
@@ -323,9 +328,10 @@ hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vect
         tables[i].dirs = base + off[i].dirs;
         tables[i].segs = base + off[i].segs;
         tables[i].idx = (const uint32_t*)(base + off[i].idx);
+        if (rests) tables[i].rest = (const float*)(base + off[i].rest);
         hipLaunchKernelGGL(k_build_tables, dim3((unsigned)((n_list + 63) / 64)), dim3(64), 0, nullptr, lw[i],
                            dirs_dev + dir_off[i], (DirTable*)(base + off[i].dirs), (Segment*)(base + off[i].segs),
-                           (uint32_t*)(base + off[i].idx));
+                           (uint32_t*)(base + off[i].idx), (float*)tables[i].rest);
         e = hipGetLastError();
     }
     // solves may run on any stream
@@ -341,10 +347,10 @@ hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vect
 
 hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vector<LevelDesc>& levels,
                         bool top_skipped, const std::vector<double4>& dirs, const std::vector<int32_t>& dir_off,
-                        const double4* dirs_dev, std::vector<LevelTable>& tables, void** mem)
+                        const double4* dirs_dev, bool rests, std::vector<LevelTable>& tables, void** mem)
 {
     try {
-        return make_tables(g, prm, levels, top_skipped, dirs, dir_off, dirs_dev, tables, mem);
+        return make_tables(g, prm, levels, top_skipped, dirs, dir_off, dirs_dev, rests, tables, mem);
     } catch (const std::bad_alloc&) {
         return hipErrorOutOfMemory;
     }

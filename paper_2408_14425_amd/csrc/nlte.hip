@@ -27,6 +27,7 @@
 
 #include "march_rows.h"
 #include "march_table.h"
+#include "segment_length.h"
 
 namespace rcx {
 namespace nl {
@@ -678,7 +679,8 @@ using LineOpSmallA = LineOpT<true>;
 // and batch), 28.8 so.
 template <class Op, bool F16>
 __global__ __launch_bounds__(march::kBlock, 4) void k_march_line(tab::LaunchArgs A, Op op,
-                                                                 const double4* __restrict__ dirs, float ds_scale)
+                                                                 const double4* __restrict__ dirs,
+                                                                 const float* __restrict__ rest, double ds_scale)
 {
     constexpr int G = Op::kW, kWaves = march::kBlock / 64, kChunk = 16;
     __shared__ float2 op_smem[Op::kSmemBytes / 8];
@@ -742,13 +744,17 @@ __global__ __launch_bounds__(march::kBlock, 4) void k_march_line(tab::LaunchArgs
             if (q < len) g = seg[(uint32_t)a + q];
             return g;
         };
+        // inclined rays: what the entry's length leaves out
+        auto left_out = [&](uint32_t q) { return rest && q < len ? rest[D.off + (uint32_t)a + q] : 0.0f; };
         tab::Segment sg = entry(l);
+        float rg = left_out(l);
         for (int s = 0; s < n_max; s += kChunk) {
             const bool in = (uint32_t)(s + l) < len;
             typename Op::StageIn r{};
             if (in) r = op.stage_load((uint32_t)(cell0 + (sg.key >> 7)));
-            const float ds = sg.ds * ds_scale;
+            const float ds = rest ? scaled_length(sg.ds, rg, ds_scale) : sg.ds;
             sg = entry(s + kChunk + l);  // the next chunk's entry, read while this one is stepped
+            rg = left_out(s + kChunk + l);
             srow[l] = in ? op.stage_make(r, ds) : typename Op::Stage{};
             march::wave_sync();
             const int n = min(kChunk, n_max - s);
@@ -1382,7 +1388,7 @@ constexpr uint32_t kLineBlocks = 16384;
 template <int G>
 hipError_t launch_line_table(bool f16, bool small_a, const LevelDesc& L, const LevelTable& T, int32_t nx, int32_t nz,
                              const LineOp& lop, int32_t u_stride, void* outb, const void* upl, int64_t slot,
-                             const int32_t* eb_b, const double4* dirs, float ds_scale, hipStream_t st)
+                             const int32_t* eb_b, const double4* dirs, double ds_scale, hipStream_t st)
 {
     // probes in plain order where tiles of 4 would leave rows empty, on grids
     // whose records (24 B a cell) stay near an L2: 194x195 2.75 -> 2.59 ms,
@@ -1398,6 +1404,7 @@ hipError_t launch_line_table(bool f16, bool small_a, const LevelDesc& L, const L
     A.slot_stride = (uint64_t)slot;
     A.ebias = eb_b;
     const unsigned grid = std::min(A.n_blocks, kLineBlocks);
+    const float* rest = ds_scale != 1.0 ? T.rest : nullptr;
     auto go = [&](auto op) {
         op.rec = lop.rec;
         op.vel = lop.vel;
@@ -1410,9 +1417,11 @@ hipError_t launch_line_table(bool f16, bool small_a, const LevelDesc& L, const L
         op.vscale = lop.vscale;
         using Op = decltype(op);
         if (f16)
-            hipLaunchKernelGGL((k_march_line<Op, true>), dim3(grid), dim3(march::kBlock), 0, st, A, op, dirs, ds_scale);
+            hipLaunchKernelGGL((k_march_line<Op, true>), dim3(grid), dim3(march::kBlock), 0, st, A, op, dirs, rest,
+                               ds_scale);
         else
-            hipLaunchKernelGGL((k_march_line<Op, false>), dim3(grid), dim3(march::kBlock), 0, st, A, op, dirs, ds_scale);
+            hipLaunchKernelGGL((k_march_line<Op, false>), dim3(grid), dim3(march::kBlock), 0, st, A, op, dirs, rest,
+                               ds_scale);
         return hipGetLastError();
     };
     return small_a ? go(LineOpT<true, G>{}) : go(LineOpT<false, G>{});
@@ -2040,16 +2049,15 @@ static int32_t formal_solve_rates(rcx_nlte* s, const double* pops, float* rates,
             hipError_t e;
             if (table && i > 0 && tr.kind == 0) {
                 const LevelTable& T = P->tables[i];
-                const float sc = (float)path;
                 if (G == 4)
                     e = launch_line_table<4>(s->f16, s->small_a, L, T, nx, nz, lop, 5 * kLB, outb, upl, slot, eb_b, dirs,
-                                             sc, st);
+                                             path, st);
                 else if (G == 2)
                     e = launch_line_table<2>(s->f16, s->small_a, L, T, nx, nz, lop, 5 * kLB, outb, upl, slot, eb_b, dirs,
-                                             sc, st);
+                                             path, st);
                 else
                     e = launch_line_table<1>(s->f16, s->small_a, L, T, nx, nz, lop, 5 * kLB, outb, upl, slot, eb_b, dirs,
-                                             sc, st);
+                                             path, st);
             } else if (table && i > 0) {
                 TableLaunch io{};
                 io.F = fop.Fb;

@@ -117,6 +117,7 @@ struct LevelTable {
     const void* dirs = nullptr;
     const void* segs = nullptr;
     const uint32_t* idx = nullptr;
+    const float* rest = nullptr;  // of every entry, what its length leaves out (segment_length.h)
     int32_t max_entries = 0;  // of the longest list, at most
     // windowed march (march_table.hip): the workgroups of window w are
     // work[win_start[w]..win_start[w + 1]) (bilinear fix: 4 taps' windows one
@@ -177,10 +178,11 @@ int32_t table_lanes(int32_t n, int64_t ncell);
 // Segment tables of every marched cascade of a plan (march_table.hip): one
 // device allocation *mem (nullptr and levels without tables when the plan has
 // none: c0_dirs != 4, or tables beyond kTableMaxBytes). `levels` holds the
-// geometry, dirs[dir_off[i]..] the directions of cascade i.
+// geometry, dirs[dir_off[i]..] the directions of cascade i. rests: with what the
+// FP32 lengths leave out (LevelTable::rest).
 hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vector<LevelDesc>& levels,
                         bool top_skipped, const std::vector<double4>& dirs, const std::vector<int32_t>& dir_off,
-                        const double4* dirs_dev, std::vector<LevelTable>& tables, void** mem);
+                        const double4* dirs_dev, bool rests, std::vector<LevelTable>& tables, void** mem);
 // The windows of one cascade (dense, or its flagged probes), where they pay;
 // replaces those T holds. dirs: the cascade's directions on the device; fix:
 // traced with the bilinear fix (the windows of each tap in turn).

@@ -854,7 +854,7 @@ static int32_t make_plan(rcx_plan* p, const rcx_grid* g, const rcx_params* prm, 
         (prm->flags & RCX_FLAG_BILINEAR_FIX ? prm->n_incl == 1 && prm->storage == RCX_STORE_F32 && !nlte
                                             : prm->n_incl == 1 || incl_slots(p) || nlte)) {
         e = build_tables(p->grid, p->prm, p->levels, p->top_skipped != 0, p->dirs_host, p->dir_off, p->dirs_dev,
-                         p->tables, &p->table_mem);
+                         nlte && prm->n_incl > 1, p->tables, &p->table_mem);
         if (e == hipErrorOutOfMemory) (void)hipGetLastError();  // the plan walks
         else if (e != hipSuccess) {
                 return hip_fail(e, "rcx_plan_create: segment tables");
