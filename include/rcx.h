@@ -235,14 +235,19 @@ int32_t rcx_plan_get_timing(rcx_plan* plan, double* ms_level_host, double* ms_ot
  * probe-major order (directions of a probe consecutive), else groups of
  * tile_p x tile_p probes x tile_d directions (tile_d a multiple of 4
  * dividing the cascade's directions), and workgroups given to the 8 XCDs in
- * chunks of xcd_chunk consecutive ones. shared_walk (0 or 1) is kept and
- * returned by rcx_plan_get_order but changes nothing: marches from segment
- * tables walk no cells. Cascades marched in windows (whose rays average 128
+ * chunks of xcd_chunk consecutive ones. shared_walk (0 or 1): with 1 and an
+ * even tile_p, a march that walks (a plan without segment tables) of a dense
+ * plan takes the rays of a group probe-fastest, so the 4 rays of a wavefront
+ * are 4 probes of one direction, and walks their cells once for all 4 (every
+ * ray still marches exactly its own segments); not the bilinear-fix kernel,
+ * the inclinations as slots or the cascade-0 J launch. Elsewhere, and with
+ * tables, the setting is kept but changes nothing. Of plans with tables,
+ * cascades marched in windows (whose rays average 128
  * cells inside the domain, on grids whose 16-wavelength fields reach 8 MB)
  * take their workgroups in an order of their own, whatever is set here, and
  * tiles that would leave a fifth of a wavefront's rows empty take the probes
  * in plain order. Defaults:
- * 4 x 4 x 32, chunk 128, on cascades with at least 256 directions;
+ * 4 x 4 x 32, chunk 128, row walks, on cascades with at least 256 directions;
  * probe-major, chunk 128, below.
  * A sparse plan's flagged-probe lists are rebuilt to follow the
  * order (synchronous). RCX_E_INVALID for a bad level or order. */
@@ -256,8 +261,9 @@ int32_t rcx_plan_get_order(const rcx_plan* plan, int32_t level, int32_t* order4_
  * plan's formal solve of up to 32
  * wavelengths on uniform fields (the march's work and memory traffic do not
  * depend on the values) for each candidate order, tile_p in {0, 2, 4, 8} x
- * tile_d in {16, 32, 64} x xcd_chunk in {32, 128, 512}, with the plan's
- * kernel timing, and keeps the fastest per cascade. cache_path (nullable): a
+ * tile_d in {16, 32, 64} x xcd_chunk in {32, 128, 512} x shared_walk in
+ * {0, 1} (for tile_p > 0, where the plan walks with one inclination), with the
+ * plan's kernel timing, and keeps the fastest per cascade. cache_path (nullable): a
  * text file of JSON lines keyed by the device (architecture, compute units)
  * and the plan's geometry, storage, flags and sparsity; a hit applies the
  * stored orders without timing, a miss appends the result. Allocates its

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -55,7 +56,10 @@ struct LevelDesc {
     // groups of tile_p x tile_p probes x tile_d directions, so the rays a
     // launch runs at one time cross a compact band of cells.
     int32_t tile_p, tile_d;
-    // kept for rcx_plan_get_order; no march reads it
+    // 1: the walking field march of a tiled order with an even tile_p runs the 4
+    // rows of a wavefront on one direction and shares their cell walk
+    // (march_rows.h, k_march_shared; bitwise the same results), else one
+    // walk per row. Marches from segment tables have no walk.
     int32_t shared_walk = 0;
     // workgroups are given to the 8 XCDs in chunks of xcd_chunk consecutive
     // ones (march_rows.h, xcd_block_chunked)
@@ -310,6 +314,17 @@ namespace rcx {
 // memory for them, walks.
 enum class PlanFor { kSolves, kNlte, kNlteWalk };
 int32_t plan_create(const rcx_grid* g, const rcx_params* prm, int32_t max_wave, PlanFor use, rcx_plan** out);
+// Tunes the launch orders of `levels` (rcx_autotune): time() runs the march
+// under the plan's current orders and gives the time of every cascade in two
+// runs; `march` names it in the cache key; shared_walk (may be empty): whether
+// that setting serves a cascade.
+struct OrderTuning {
+    std::string march;
+    std::vector<int32_t> levels;
+    std::function<bool(int32_t)> shared_walk;
+    std::function<int32_t(double* ms_level)> time;
+};
+int32_t tune_orders(rcx_plan* p, const OrderTuning& t, const char* cache_path);
 // A small atmosphere of a batch: its field preparation on the plan's own
 // workspace in 16-lane batches (plan_enqueue_prep), and its cascades as tasks
 // (plan_table_tasks: one per marched cascade into tasks[level], empty where

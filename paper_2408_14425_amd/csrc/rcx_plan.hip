@@ -1125,24 +1125,68 @@ int32_t rcx_plan_get_order(const rcx_plan* p, int32_t level, int32_t* order4_hos
 int32_t rcx_autotune(rcx_plan* p, const char* cache_path, hipStream_t st)
 {
     if (!p) return fail(RCX_E_INVALID, "rcx_autotune: null plan");
-    const int32_t nx = p->grid.nx, nz = p->grid.nz;
-    const int64_t ncell = (int64_t)nx * nz;
+    const int64_t ncell = (int64_t)p->grid.nx * p->grid.nz;
     const int32_t n_wave = std::min(p->max_wave, 2 * batch_width());
-    std::vector<int32_t> tun;  // the cascades whose launch order is tuned (a windowed one has its own)
+    const bool tables = use_tables(p);
+    OrderTuning t;  // the cascades whose launch order is tuned (a windowed one has its own)
     for (int32_t i = 0; i < p->n_casc; ++i)
         if (p->levels[i].nd >= kTileMinDirs && !(p->top_skipped && i == p->n_casc - 1) &&
-            !(use_tables(p) && n_wave >= batch_width() && !p->tables[i].win_start.empty()))
-            tun.push_back(i);
+            !(tables && n_wave >= batch_width() && !p->tables[i].win_start.empty()))
+            t.levels.push_back(i);
+    t.march = "/w" + std::to_string(n_wave) + (tables ? "/table" : "/walk2");  // the march the orders are tuned on
+    // the shared walk serves the basic march of a dense plan with one
+    // inclination (with the bilinear fix, only its top marched cascade);
+    // elsewhere its setting changes nothing and is kept 0
+    t.shared_walk = [p, tables](int32_t i) {
+        return !tables && !p->mask_dev && p->prm.n_incl == 1 &&
+               (!(p->prm.flags & RCX_FLAG_BILINEAR_FIX) || !p->levels[i].has_up);
+    };
+    const bool timing = p->timing;
+    float* buf = nullptr;
+    void* ws = nullptr;
+    const size_t nfield = (size_t)n_wave * ncell, ws_bytes = ws_layout(p, n_wave).total;
+    // the plan's own solve on uniform fields
+    t.time = [&](double* ms) {
+        if (!buf) {
+            hipError_t e = hipMalloc(&buf, sizeof(float) * 3 * nfield);
+            if (e == hipSuccess && !p->ws_own) e = hipMalloc(&ws, ws_bytes);
+            if (e != hipSuccess) return fail(RCX_E_NOMEM, "rcx_autotune: temporary fields");
+            e = launch_fill_f32(buf, (int64_t)2 * nfield, 1.0f, st);
+            if (e != hipSuccess) return hip_fail(e, "rcx_autotune");
+        }
+        double other = 0.0;
+        int64_t nl = 0, ns = 0;
+        int32_t rc = RCX_OK;
+        for (int r = 0; r < 3 && rc == RCX_OK; ++r) {
+            p->timing = r > 0;
+            rc = rcx_formal_solve(p, n_wave, buf, buf + nfield, buf + 2 * nfield, ws, ws_bytes, st);
+        }
+        return rc == RCX_OK ? rcx_plan_get_timing(p, ms, &other, &nl, &ns) : rc;
+    };
+    const int32_t rc = tune_orders(p, t, cache_path);
+    p->timing = timing;
+    if (buf) {
+        (void)hipStreamSynchronize(st);
+        (void)hipFree(buf);
+        if (ws) (void)hipFree(ws);
+    }
+    return rc;
+}
+}  // extern "C"
+
+namespace rcx {
+int32_t tune_orders(rcx_plan* p, const OrderTuning& t, const char* cache_path)
+{
+    const std::vector<int32_t>& tun = t.levels;
     if (tun.empty()) return ok();
     int dev = 0;
     RCX_HIP_TRY(hipGetDevice(&dev));
     hipDeviceProp_t prop;
     RCX_HIP_TRY(hipGetDeviceProperties(&prop, dev));
     std::ostringstream key;
-    key << prop.gcnArchName << "/" << prop.multiProcessorCount << "cu/" << nx << "x" << nz << "/c" << p->n_casc
-        << "/d" << p->prm.c0_dirs << "/t1=" << p->prm.c0_t1 << "/r" << p->prm.t_rule << "/s" << p->prm.storage
-        << "/i" << p->prm.n_incl << "/f" << (p->prm.flags & RCX_FLAG_BILINEAR_FIX) << "/w" << n_wave
-        << (use_tables(p) ? "/table" : "/walk2");  // the march the orders were tuned on
+    key << prop.gcnArchName << "/" << prop.multiProcessorCount << "cu/" << p->grid.nx << "x" << p->grid.nz << "/c"
+        << p->n_casc << "/d" << p->prm.c0_dirs << "/t1=" << p->prm.c0_t1 << "/r" << p->prm.t_rule << "/s"
+        << p->prm.storage << "/i" << p->prm.n_incl << "/f" << (p->prm.flags & RCX_FLAG_BILINEAR_FIX) << t.march;
     if (p->mask_dev) key << "/sparse" << p->levels[0].n_active;
     const std::string k = key.str();
     const std::string pre = "{\"key\": \"" + k + "\", \"orders\": \"";
@@ -1163,64 +1207,37 @@ int32_t rcx_autotune(rcx_plan* p, const char* cache_path, hipStream_t st)
             return rc;
         }
     }
-    // time candidate orders on uniform fields (the march's work and memory
-    // traffic do not depend on the values)
     struct Cand {
-        int32_t tp, td, ch;
+        int32_t tp, td, ch, sw;
     };
+    auto shared = [&](int32_t i) { return t.shared_walk && t.shared_walk(i); };
+    bool any_shared = false;
+    for (int32_t i : tun) any_shared = any_shared || shared(i);
     std::vector<Cand> cands;
     for (int32_t ch : {32, 128, 512}) {
-        cands.push_back({0, 0, ch});
+        cands.push_back({0, 0, ch, 0});
         for (int32_t tp : {2, 4, 8})
             for (int32_t td : {16, 32, 64})
-                cands.push_back({tp, td, ch});
+                for (int32_t sw : {0, 1})
+                    if (sw == 0 || any_shared) cands.push_back({tp, td, ch, sw});
     }
-    std::vector<LevelDesc> saved = p->levels;
-    const bool timing = p->timing;
-    float* buf = nullptr;
-    void* ws = nullptr;
-    const size_t nfield = (size_t)n_wave * ncell;
-    hipError_t e = hipMalloc(&buf, sizeof(float) * 3 * nfield);
-    const size_t ws_bytes = ws_layout(p, n_wave).total;
-    if (e == hipSuccess && !p->ws_own) e = hipMalloc(&ws, ws_bytes);
-    if (e != hipSuccess) {
-        if (buf) (void)hipFree(buf);
-        return fail(RCX_E_NOMEM, "rcx_autotune: temporary fields");
-    }
+    auto set = [&](const Cand& c, int32_t i) {
+        const int32_t td = c.tp > 0 && p->levels[i].nd % c.td != 0 ? 4 : c.td;
+        return rcx_plan_set_order(p, i, c.tp, td, c.ch, shared(i) ? c.sw : 0);
+    };
+    const std::vector<LevelDesc> saved = p->levels;
     int32_t rc = RCX_OK;
-    e = launch_fill_f32(buf, (int64_t)2 * nfield, 1.0f, st);
     std::vector<std::vector<double>> ms(cands.size(), std::vector<double>(p->n_casc, 0.0));
-    std::vector<double> lvl(p->n_casc);
-    double other = 0.0;
-    int64_t nl = 0, ns = 0;
-    for (size_t c = 0; c < cands.size() && rc == RCX_OK && e == hipSuccess; ++c) {
-        for (int32_t i : tun) {
-            const int32_t td = cands[c].tp > 0 && p->levels[i].nd % cands[c].td != 0 ? 4 : cands[c].td;
-            rc = rcx_plan_set_order(p, i, cands[c].tp, td, cands[c].ch, 0);
-            if (rc != RCX_OK) break;
-        }
-        if (rc != RCX_OK) break;
-        p->timing = false;
-        rc = rcx_formal_solve(p, n_wave, buf, buf + nfield, buf + 2 * nfield, ws, ws_bytes, st);
-        if (rc != RCX_OK) break;
-        p->timing = true;
-        for (int r = 0; r < 2 && rc == RCX_OK; ++r)
-            rc = rcx_formal_solve(p, n_wave, buf, buf + nfield, buf + 2 * nfield, ws, ws_bytes, st);
-        if (rc == RCX_OK) rc = rcx_plan_get_timing(p, lvl.data(), &other, &nl, &ns);
-        ms[c] = lvl;
+    for (size_t c = 0; c < cands.size() && rc == RCX_OK; ++c) {
+        for (int32_t i : tun)
+            if (rc == RCX_OK) rc = set(cands[c], i);
+        if (rc == RCX_OK) rc = t.time(ms[c].data());
     }
-    p->timing = timing;
-    (void)hipStreamSynchronize(st);
-    (void)hipFree(buf);
-    if (ws) (void)hipFree(ws);
-    if (e != hipSuccess && rc == RCX_OK) rc = hip_fail(e, "rcx_autotune");
     if (rc != RCX_OK) {
-        p->levels = saved;
-        if (p->mask_dev) {
-            const std::vector<uint8_t> flags = p->active_host;
-            (void)rcx_plan_set_active_host(p, flags.data(), nullptr);
-        }
-        return rc;
+        const std::string msg = g_last_msg;
+        for (int32_t i = 0; i < p->n_casc; ++i)
+            (void)rcx_plan_set_order(p, i, saved[i].tile_p, saved[i].tile_d, saved[i].xcd_chunk, saved[i].shared_walk);
+        return fail(rc, msg);
     }
     std::ostringstream orders, times;
     for (size_t q = 0; q < tun.size(); ++q) {
@@ -1228,11 +1245,11 @@ int32_t rcx_autotune(rcx_plan* p, const char* cache_path, hipStream_t st)
         size_t best = 0;
         for (size_t c = 1; c < cands.size(); ++c)
             if (ms[c][i] < ms[best][i]) best = c;
-        const int32_t td = cands[best].tp > 0 && p->levels[i].nd % cands[best].td != 0 ? 4 : cands[best].td;
-        rc = rcx_plan_set_order(p, i, cands[best].tp, td, cands[best].ch, 0);
+        rc = set(cands[best], i);
         if (rc != RCX_OK) return rc;
-        orders << (q ? "," : "") << i << ":" << cands[best].tp << ":" << p->levels[i].tile_d << ":" << cands[best].ch
-               << ":0";
+        const LevelDesc& L = p->levels[i];
+        orders << (q ? "," : "") << i << ":" << L.tile_p << ":" << L.tile_d << ":" << L.xcd_chunk << ":"
+               << L.shared_walk;
         times << (q ? "," : "") << i << ":" << ms[best][i] / 2.0 << "/" << ms[0][i] / 2.0;
     }
     if (cache_path) {
@@ -1241,6 +1258,9 @@ int32_t rcx_autotune(rcx_plan* p, const char* cache_path, hipStream_t st)
     }
     return ok();
 }
+}  // namespace rcx
+
+extern "C" {
 
 int32_t rcx_plan_destroy(rcx_plan* p)
 {
