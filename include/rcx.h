@@ -453,11 +453,17 @@ int32_t rcx_nlte_stat_eq(rcx_nlte* s, const float* rates, double* pops_inout,
 int32_t rcx_nlte_iterate(rcx_nlte* s, double* pops_inout, int32_t max_iter, double tol,
                          int32_t* iters_host, double* last_change_host, hipStream_t stream);
 
-/* Launch orders of the solver's marches: rcx_autotune on the solver's own
- * plan (its formal solve of 16 wavelengths timed for each candidate order,
- * cache_path as there). The line and continuum marches take the chosen
- * orders too; every result is bitwise the same under any order (each ray's
- * arithmetic does not depend on where it runs). Synchronises the stream.
+/* Launch orders of the solver's marches, as rcx_autotune for a plan: for every
+ * cascade with at least 256 directions, times the line march of a group of
+ * wavelength batches and the continuum march of one (where the cascade is not
+ * marched in windows), as often as a formal solution takes them, for each
+ * candidate order, on uniform fields, and keeps the fastest (cache_path as
+ * there, under keys of the solver's own: its line batches, their groups, its
+ * continuum batches and the profile in use). Works before
+ * rcx_nlte_set_atmosphere too; overwrites the solver's cascade buffers, which
+ * hold nothing between calls. Every result is bitwise the same under any order
+ * (each ray's arithmetic does not depend on where it runs). Synchronises the
+ * stream. A solver without segment tables tunes its plan's solve.
  * Errors: as rcx_autotune. */
 int32_t rcx_nlte_autotune(rcx_nlte* s, const char* cache_path, hipStream_t stream);
 

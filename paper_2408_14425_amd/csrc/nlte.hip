@@ -2466,9 +2466,96 @@ int32_t rcx_nlte_dims(const rcx_nlte* s, int32_t* nl, int32_t* nt)
 int32_t rcx_nlte_autotune(rcx_nlte* s, const char* cache_path, hipStream_t stream)
 {
     if (!s) return nlte_fail(RCX_E_INVALID, "rcx_nlte_autotune: null solver");
-    // the solver marches with its plan's launch orders (results do not
-    // depend on them): tune them on the plan's own formal solve
-    return rcx_autotune(s->plan, cache_path, stream);
+    rcx_plan* P = s->plan;
+    if (!P->table_mem) return rcx_autotune(P, cache_path, stream);  // the solver walks, as the plan's solves do
+    // the line march of a group of batches, and the continuum's of one batch
+    // where it is marched whole, as often as a formal solution launches them
+    int32_t first = -1, n_line = 0;
+    for (int32_t b = 0; b < (int32_t)s->batches.size(); ++b)
+        if (s->atom.t[s->batches[b].trans].kind == 0) {
+            if (first < 0) first = b;
+            ++n_line;
+        }
+    const int32_t G = first >= 0 && s->group > 1 ? line_group(s, first, s->group) : 1;
+    const double w_line = (double)n_line / G * P->prm.n_incl, w_cont = s->n_cont_batches;
+    OrderTuning t;
+    for (int32_t i = 1; i < P->n_casc; ++i)
+        if (P->levels[i].nd >= kTileMinDirs && !(P->top_skipped && i == P->n_casc - 1) &&
+            (n_line > 0 || P->tables[i].win_start.empty()))
+            t.levels.push_back(i);
+    t.march = "/nlte/l" + std::to_string(n_line) + "x" + std::to_string(G) + "/c" + std::to_string(s->n_cont_batches) +
+              (s->small_a ? "/a0" : "/a");
+    const int32_t nx = P->grid.nx, nz = P->grid.nz;
+    const int64_t nc = s->ncell;
+    float* buf = nullptr;  // cell records, velocities and fields, uniform: their values change little
+    hipEvent_t ev[3] = {};
+    t.time = [&](double* ms) -> int32_t {
+        hipError_t e = hipSuccess;
+        const int64_t n_buf = nc * (4 + 2 + 2 * kLB);
+        if (!buf) {
+            if (hipMalloc(&buf, sizeof(float) * n_buf) != hipSuccess) {
+                buf = nullptr;
+                (void)hipGetLastError();
+                return nlte_fail(RCX_E_NOMEM, "rcx_nlte_autotune: temporary fields");
+            }
+            e = launch_fill_f32(buf, n_buf, 1e-4f, stream);
+            for (auto& v : ev)
+                if (e == hipSuccess) e = hipEventCreate(&v);
+        }
+        LineOp lop{};
+        lop.rec = (const float4*)buf;
+        lop.vel = (const float2*)(buf + 4 * nc);
+        lop.tabc = s->vtabc;
+        lop.n_a = s->n_ac;
+        lop.u_b = s->bconst + (int64_t)std::max(first, 0) * 5 * kLB + 1 * kLB;
+        lop.ncell = (uint32_t)nc;
+        lop.da_sqrtpi = (float)(s->da_c / std::sqrt(kPi));
+        for (int32_t i : t.levels) {
+            const LevelDesc& L = P->levels[i];
+            const LevelTable& T = P->tables[i];
+            const double4* dirs = P->dirs_dev + P->dir_off[i];
+            const void* up = L.has_up ? s->casc[1] : nullptr;
+            ms[i] = 0.0;
+            for (int r = 0; r < 3 && e == hipSuccess; ++r) {
+                (void)hipEventRecord(ev[0], stream);
+                if (n_line > 0) {
+                    auto line = [&](auto g) {
+                        return launch_line_table<decltype(g)::value>(s->f16, s->small_a, L, T, nx, nz, lop, 5 * kLB,
+                                                                     s->casc[0], up, s->casc_slot, s->ebias, dirs, 1.0,
+                                                                     stream);
+                    };
+                    e = G == 4   ? line(std::integral_constant<int, 4>{})
+                        : G == 2 ? line(std::integral_constant<int, 2>{})
+                                 : line(std::integral_constant<int, 1>{});
+                }
+                (void)hipEventRecord(ev[1], stream);
+                if (e == hipSuccess && s->n_cont_batches > 0 && T.win_start.empty()) {
+                    TableLaunch io{};
+                    io.F = buf + 6 * nc;
+                    io.up = up;
+                    io.out = s->casc[0];
+                    io.f16 = s->f16;
+                    io.ebias = s->ebias;
+                    e = launch_march_table(L, T, nx, nz, io, stream);
+                }
+                (void)hipEventRecord(ev[2], stream);
+                float line_ms = 0.0f, cont_ms = 0.0f;
+                if (e == hipSuccess) e = hipEventSynchronize(ev[2]);
+                if (e == hipSuccess) e = hipEventElapsedTime(&line_ms, ev[0], ev[1]);
+                if (e == hipSuccess) e = hipEventElapsedTime(&cont_ms, ev[1], ev[2]);
+                if (r > 0) ms[i] += w_line * line_ms + w_cont * cont_ms;
+            }
+        }
+        return e == hipSuccess ? RCX_OK : rcx::hip_fail(e, "rcx_nlte_autotune");
+    };
+    const int32_t rc = tune_orders(P, t, cache_path);
+    if (buf) {
+        (void)hipStreamSynchronize(stream);
+        (void)hipFree(buf);
+    }
+    for (auto v : ev)
+        if (v) (void)hipEventDestroy(v);
+    return rc;
 }
 
 int32_t rcx_nlte_set_timing(rcx_nlte* s, int32_t enable)

@@ -40,6 +40,9 @@ inline FastDiv make_fastdiv(uint32_t d)
 // along an axis.
 constexpr uint32_t kMaxGridX = (1u << 24) - 8;
 
+// Cascades with at least as many directions are tiled (LevelDesc::tile_p).
+constexpr int32_t kTileMinDirs = 256;
+
 constexpr uint32_t kDecodeReady = 0x52435844u;
 
 // Geometry of one cascade as the march/merge kernel sees it.

@@ -18,10 +18,9 @@
 
 namespace rcx {
 
-// Ray order of the upper cascades (see LevelDesc::tile_p).
-constexpr int32_t kTileMinDirs = 256;
 // Cascades marched two wavelength batches at a time (see rcx_formal_solve).
 constexpr int32_t kPairMaxDirs = 256;
+// Ray order of the upper cascades (see LevelDesc::tile_p).
 constexpr int32_t kTileProbes = 4;
 constexpr int32_t kTileDirs = 32;
 

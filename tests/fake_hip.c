@@ -74,6 +74,8 @@ int hipMemset(void* d, int v, size_t n) { memset(d, v, n); return kOk; }
 int hipGetLastError(void) { int e = last_error; last_error = kOk; return e; }
 const char* hipGetErrorName(int e) { return e == kOutOfMemory ? "hipErrorOutOfMemory" : "hipError"; }
 const char* hipGetErrorString(int e) { return hipGetErrorName(e); }
+/* every field 0 (the structure holds 1472 bytes) */
+int hipGetDevicePropertiesR0600(void* prop, int d) { (void)d; memset(prop, 0, 1472); return kOk; }
 int hipGetDevice(int* d) { *d = 0; return kOk; }
 int hipDeviceSynchronize(void) { return kOk; }
 int hipGetSymbolAddress(void** p, const void* sym)
