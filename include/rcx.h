@@ -328,7 +328,8 @@ int32_t rcx_batch_launches(const rcx_batch* b, int32_t* march_host, int32_t* all
  * (2, 32), (4, 16), (4, 32), (4, 64), (8, 32)} (rcx_batch_set_order) on
  * these inputs and keep the fastest: *best_host = tile_probes * 1000 +
  * tile_dirs. cache_path (or NULL): a text file of JSON lines keyed by the
- * batch's shapes; a hit skips timing, a miss appends the result. */
+ * device, the march, the cascade intervals and the batch's shapes; a hit skips
+ * timing, a miss appends the result. */
 int32_t rcx_batch_autotune(rcx_batch* b, const float* const* chi_host, const float* const* eta_host,
                            float* const* J_host, const char* cache_path, int32_t* best_host, hipStream_t stream);
 int32_t rcx_batch_destroy(rcx_batch* b);

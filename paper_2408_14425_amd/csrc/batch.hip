@@ -403,9 +403,18 @@ int32_t rcx_batch_autotune(rcx_batch* s, const float* const* chi, const float* c
                            const char* cache_path, int32_t* best_rays_host, hipStream_t st)
 {
     if (!s || !chi || !eta || !J || !best_rays_host) return bfail(RCX_E_INVALID, "rcx_batch_autotune: null argument");
-    // cache key: the batch's shapes
+    // cache key: the device, the march the orders are tuned on, the cascade
+    // intervals and the batch's shapes
+    int dev = 0;
+    RCX_HIP_TRY(hipGetDevice(&dev));
+    hipDeviceProp_t prop;
+    RCX_HIP_TRY(hipGetDeviceProperties(&prop, dev));
+    bool tables = true;
+    for (const rcx_plan* P : s->plans) tables = tables && P->table_mem;
+    const rcx_params& prm = s->plans[0]->prm;
     std::ostringstream key;
-    key << "v2_" << (s->f16 ? "f16" : "f32");
+    key << prop.gcnArchName << "_" << prop.multiProcessorCount << "cu_" << (tables ? "table" : "walk") << "_t"
+        << prm.c0_t1 << "_r" << prm.t_rule << "_" << (s->f16 ? "f16" : "f32");
     for (int32_t a = 0; a < s->n_atm; ++a)
         if (s->plans[a]->mask_dev) key << "_sparse" << a << "_" << s->plans[a]->levels[0].n_active;
     for (int32_t a = 0; a < s->n_atm; ++a)
