@@ -285,12 +285,16 @@ hipError_t make_tables(const rcx_grid& g, const rcx_params& prm, const std::vect
         const double far_x = std::max((L.px - 1) * L.s + std::floor(0.5 * L.s), g.nx - 1.0);
         const double far_z = std::max((L.pz - 1) * L.s + std::floor(0.5 * L.s), g.nz - 1.0);
         const int32_t nc = W.fix ? tab::kFixClasses : 1;
+        // (before the host holds a header for every list)
+        const double least = (sizeof(DirTable) + (8.0 + tab::kSegPad) * sizeof(Segment)) * L.nd * nc;
+        if ((double)total + least > (double)kTableMaxBytes) return hipSuccess;
         dt.resize(first[i] + (size_t)L.nd * nc);
         first[i + 1] = dt.size();
         double n_seg = 0.0, n_idx = 0.0;
         for (int32_t k = 0; k < L.nd * nc; ++k) {
             const Line d = list_line(W, dirs[dir_off[i] + k / nc], k % nc);
             const double len = std::max(d.t1 - d.t0, 0.0), wx = std::fabs(d.x), wz = std::fabs(d.z);
+            if (!(len * (wx + wz) < 1e9)) return hipSuccess;  // (intervals near the largest double, with the fix)
             // keys are 32-bit byte offsets with sign: where a ray can cross a
             // cell 2^24 cells away (within a few percent of the largest grids,
             // with probes past the edge) the plan walks

@@ -70,3 +70,28 @@ def test_window_bins_follow_the_lists(tmp_path, nx, nz, windowed, most):
         bins = mallocs()[2:2 + 2 * n:2]
         assert all(b <= {most} for b in bins), bins
     """)
+
+
+@pytest.mark.parametrize("t1", [1e306, 1e308, 1.7e308])
+def test_intervals_near_the_largest_double(tmp_path, t1):
+    """With the bilinear fix the end of an interval overflows; such lists are
+    not sized from infinities, the plan walks."""
+    run(tmp_path, f"""
+        p = plan(64, 64, flags=1, c0_t1={t1})
+        assert all(b < 2**31 for b in mallocs())
+        ls = solve(p, 64, 64)
+        if count(ls, "k_march_fix_table") == 0:
+            assert count(ls, "k_march_fix") > 0
+    """)
+
+
+def test_headers_of_lists_that_are_too_many(tmp_path):
+    """A plan whose lists cannot fit makes no host copy of their headers: 12
+    cascades on 8^2 have 2^24 directions, 0.7 GB of them on host and (here)
+    device each, 1.1 GB of headers."""
+    run(tmp_path, """
+        p = plan(8, 8, n_cascades=12, c0_t1=1e-6)
+        assert count(launches(), "k_build_tables") == 0
+        peak = [int(l.split()[1]) for l in open("/proc/self/status") if l.startswith("VmHWM")][0]
+        assert peak < 2_000_000, peak
+    """)
