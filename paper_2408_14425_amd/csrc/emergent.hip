@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_emergent(int32_t nx, int32_t nz, 
     __syncthreads();
 
     // ---- the segments (walk_ray, march_rows.h: the same arithmetic)
-    const int j = B.r0 + group * kRays + lane;
+    const int64_t j = (int64_t)B.r0 + group * kRays + lane;  // (beams of nearly 2^31 rays)
     const double s = (double)j + 0.5 - 0.5 * (double)B.n_rays;
     const double cx = B.ox0 + s * B.px, cz = B.oz0 + s * B.pz;
     const double kx = floor(cx), kz = floor(cz), fx = cx - kx, fz = cz - kz;
