@@ -137,8 +137,12 @@ int32_t rcx_params_default(rcx_params* p);
  * or with 8 inclinations and FP32 cascades, also hold segment tables of their
  * directions (about 12 B per direction and cell crossed: 50 MB at 1024^2);
  * with the bilinear fix, flatland and FP32 cascades, 16 lists per direction
- * (280 MB at 512^2, 860 MB at 1024^2). Tables beyond 2 GiB, or that the device
- * has no memory for, are left out and the solves walk the grid.
+ * (280 MB at 512^2, 860 MB at 1024^2). Where the tables are left out the solves
+ * walk the grid: beyond 2 GiB, where the device has no memory for them (beside
+ * the workspace), and where a 32-bit offset would not reach (rays that cross a
+ * cell 2^24 cells from their probe's, on ragged grids of nearly 2^24 cells; long
+ * strips whose cascades hold 2^28 rays, 2^30 with FP32 storage). Cascades whose
+ * window lists find no memory are marched whole.
  * Errors: RCX_E_INVALID (null, nx/nz/max_wave <= 0, c0_dirs <= 0,
  * c0_t1 <= 0, n_cascades outside [1, 16], n_incl outside [1, 16], unknown
  * flags); RCX_E_UNSUPPORTED (unknown storage, too many top-cascade
@@ -159,8 +163,8 @@ int32_t rcx_plan_create(const rcx_grid* g, const rcx_params* p, int32_t max_wave
  * each cascade [n_cascades]. Builds the flagged-probe lists on the host and
  * copies them to plan-owned device memory (synchronous; memory the size of
  * one int32 per flagged probe plus one byte per cell).
- * Errors: RCX_E_INVALID (null plan); RCX_E_HIP (allocation or copy: the plan
- * is then dense). */
+ * Errors: RCX_E_INVALID (null plan); RCX_E_HIP (device allocation or copy),
+ * RCX_E_NOMEM (host): the plan is then dense. */
 int32_t rcx_plan_set_active_host(rcx_plan* plan, const uint8_t* active_host, int64_t* level_active_host);
 
 /* Bytes of device workspace for a solve of n_wave wavelengths. Where cascades
@@ -197,8 +201,8 @@ int32_t rcx_formal_solve(rcx_plan* plan, int32_t n_wave, const float* chi, const
  * no hipMalloc, hipFree or allocating library routine; the plan must not
  * have kernel timing enabled (it records events).
  * Errors: RCX_E_INVALID (null arrays, n_wave outside [1, max_wave], timing
- * enabled); RCX_E_WORKSPACE when the solve needs more than the 64 MiB (e.g.
- * more than about 256^2 cells x 16 wavelengths: use rcx_formal_solve);
+ * enabled); RCX_E_WORKSPACE when the solve needs more than the 64 MiB (more
+ * than about 320^2 cells x 16 wavelengths: use rcx_formal_solve);
  * RCX_E_NONFINITE; RCX_E_HIP. */
 int32_t rcx_formal_solve_noalloc(rcx_plan* plan, int32_t n_wave, const float* chi, const float* eta, float* J,
                                  hipStream_t stream);
@@ -278,12 +282,15 @@ int32_t rcx_plan_destroy(rcx_plan* plan);
 /* ================================================================ batches
  * Many formal solutions at once (several atmospheres, each with its
  * wavelength batches; every one an independent formal solution, Secs. 2.3
- * and 3.2). Every atmosphere runs through a plan of its own (the launches of
- * rcx_formal_solve); the whole sequence is captured into a HIP graph and
- * replayed, re-captured when the input or output pointers change.
- * Atmospheres whose every cascade holds at least 2^19 rays (about 512^2 and
- * up) fill the GPU alone and follow one another; smaller ones run beside
- * them on up to three further branches of the graph. */
+ * and 3.2). Every atmosphere has a plan of its own; the whole sequence is
+ * captured into a HIP graph and replayed, re-captured when the input or output
+ * pointers change. Atmospheres whose every cascade holds at least 2^19 rays
+ * (about 512^2 and up) fill the GPU alone: they run through their plans' solves
+ * (the launches of rcx_formal_solve), one after another. Smaller ones share
+ * launches, one per cascade for all of them (more where its grid would pass
+ * 2^32 work items), where their plans hold tables, no windows and workspace for
+ * all their wavelengths at once; the others run through their plans, on up to
+ * three further branches of the graph beside the rest. */
 typedef struct rcx_batch rcx_batch;
 
 /* n_atm atmospheres with grids[a] and n_wave[a] wavelengths. p as for

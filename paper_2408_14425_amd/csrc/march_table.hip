@@ -360,9 +360,8 @@ hipError_t build_tables(const rcx_grid& g, const rcx_params& prm, const std::vec
     }
 }
 
-int32_t table_lanes(int32_t n, int64_t ncell)
+int32_t table_lanes(int32_t n)
 {
-    (void)ncell;
     int32_t lanes = 1;
     while (lanes < n) lanes *= 2;
     return std::min(lanes, (int32_t)tab::kLB);
@@ -409,7 +408,7 @@ void fix_probes(tab::LaunchArgs& A)
 
 // Probes in plain order (along the directions' minor axis, PW at a time)
 // where tiled sub-blocks would leave more than a fifth of their rows empty:
-// 333x200 x 19 wavelengths 541 -> 492 us, x 3 209 -> 188, 100x140 x 32 124 ->
+// 333x200 x 19 wavelengths 512 -> 468 us, x 3 209 -> 188, 100x140 x 32 124 ->
 // 116; with less waste the tiles' locality is worth more (600x420 x 20 3.19
 // ms in tiles, 3.29 plain from 8 % on, 3.51 from 2 %).
 constexpr double kPlainWaste = 1.25;

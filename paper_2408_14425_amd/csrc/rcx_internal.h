@@ -179,8 +179,8 @@ struct CascIO {
 // Wavelengths per batch of the field and cascade layouts.
 int32_t batch_width();
 // Lanes (wavelengths) a row of the table march takes for the last n < 16
-// wavelengths of a solve on ncell cells.
-int32_t table_lanes(int32_t n, int64_t ncell);
+// wavelengths of a solve.
+int32_t table_lanes(int32_t n);
 
 // Segment tables of every marched cascade of a plan (march_table.hip): one
 // device allocation *mem (nullptr and levels without tables when the plan has

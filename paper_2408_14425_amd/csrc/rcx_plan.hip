@@ -599,7 +599,7 @@ int32_t solve_tables(rcx_plan* p, int32_t n_wave, int32_t last_lanes, float* J, 
         char* bufs[2] = {casc, casc + per * nb};
         // the last, narrower batch goes along with the last whole ones: the
         // cascades marched whole take one launch, which its few, long rays do
-        // not fill alone (333 x 200 x 19 wavelengths 613 -> 541 us, 64^2 x 17
+        // not fill alone (333 x 200 x 19 wavelengths 590 -> 512 us, 64^2 x 17
         // 55 -> 35, 700^2 x 20 8.3 -> 8.0 ms). Where the buffers hold both, and
         // both stay in the last-level cache (256 MB): beyond it each chain of
         // cascades is faster by itself (1024^2 x 24 31.4 ms along, 31.0 apart)
@@ -688,7 +688,7 @@ int32_t enqueue_solve(rcx_plan* p, int32_t n_wave, const float* chi, const float
         return ok();
     }
     const bool tables = use_tables(p);
-    const int32_t last_lanes = tables && n_wave % lb != 0 ? table_lanes(n_wave % lb, ncell) : lb;
+    const int32_t last_lanes = tables && n_wave % lb != 0 ? table_lanes(n_wave % lb) : lb;
     int32_t rc = enqueue_prep(p, n_wave, chi, eta, w, ws, last_lanes, st);
     if (rc != RCX_OK) return rc;
     rc = tables ? solve_tables(p, n_wave, last_lanes, J, w, ws, st) : solve_batches(p, n_wave, J, w, ws, st);

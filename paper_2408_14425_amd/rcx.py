@@ -272,7 +272,8 @@ class Plan:
 
     def set_order(self, level: int, tile_p: int, tile_d: int = 32, xcd_chunk: int = 128, shared_walk: int = 0):
         """Launch order of cascade `level` (tile_p = 0: probe-major;
-        shared_walk = 1: one cell walk for the 4 rays of a wavefront)."""
+        shared_walk = 1: one cell walk for the 4 rays of a wavefront, in
+        plans without segment tables)."""
         _check(load().rcx_plan_set_order(self.handle, int(level), int(tile_p), int(tile_d), int(xcd_chunk),
                                          int(shared_walk)),
                "rcx_plan_set_order")
@@ -782,7 +783,7 @@ def _ptr_array(ts, what: str):
 class Batch:
     """Owns an ``rcx_batch``: formal solutions of several atmospheres (grids
     ``shapes[a] = (nx, nz)``, ``n_wave[a]`` wavelengths) as one captured
-    graph of list-scheduled launches."""
+    graph: large ones through their plans, small ones sharing launches."""
 
     def __init__(self, shapes, n_wave, voxel_scale=1.0, storage: int = RCX_STORE_F32, c0_t1: float = 1.5,
                  t_rule: int = RCX_T_GEOMETRIC, check_input: bool = False):
