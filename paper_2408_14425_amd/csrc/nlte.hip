@@ -677,7 +677,9 @@ using LineOpSmallA = LineOpT<true>;
 // measured 1.5 to 4 % faster than chunks of 32 (37 KB). Line launches of
 // 512^2 x 160 wavelengths 33.9 ms with the cell walk (24 instructions per step
 // and batch), 28.8 so.
-template <class Op, bool F16>
+// REST: inclined rays, whose lengths are scaled by ds_scale with what the
+// FP32 lengths leave out (rest; a test of the pointer cost 0.5 %).
+template <class Op, bool F16, bool REST>
 __global__ __launch_bounds__(march::kBlock, 4) void k_march_line(tab::LaunchArgs A, Op op,
                                                                  const double4* __restrict__ dirs,
                                                                  const float* __restrict__ rest, double ds_scale)
@@ -744,15 +746,14 @@ __global__ __launch_bounds__(march::kBlock, 4) void k_march_line(tab::LaunchArgs
             if (q < len) g = seg[(uint32_t)a + q];
             return g;
         };
-        // inclined rays: what the entry's length leaves out
-        auto left_out = [&](uint32_t q) { return rest && q < len ? rest[D.off + (uint32_t)a + q] : 0.0f; };
+        auto left_out = [&](uint32_t q) { return REST && q < len ? rest[D.off + (uint32_t)a + q] : 0.0f; };
         tab::Segment sg = entry(l);
         float rg = left_out(l);
         for (int s = 0; s < n_max; s += kChunk) {
             const bool in = (uint32_t)(s + l) < len;
             typename Op::StageIn r{};
             if (in) r = op.stage_load((uint32_t)(cell0 + (sg.key >> 7)));
-            const float ds = rest ? scaled_length(sg.ds, rg, ds_scale) : sg.ds;
+            const float ds = REST ? scaled_length(sg.ds, rg, ds_scale) : sg.ds;
             sg = entry(s + kChunk + l);  // the next chunk's entry, read while this one is stepped
             rg = left_out(s + kChunk + l);
             srow[l] = in ? op.stage_make(r, ds) : typename Op::Stage{};
@@ -1416,12 +1417,13 @@ hipError_t launch_line_table(bool f16, bool small_a, const LevelDesc& L, const L
         op.da_sqrtpi = lop.da_sqrtpi;
         op.vscale = lop.vscale;
         using Op = decltype(op);
-        if (f16)
-            hipLaunchKernelGGL((k_march_line<Op, true>), dim3(grid), dim3(march::kBlock), 0, st, A, op, dirs, rest,
-                               ds_scale);
-        else
-            hipLaunchKernelGGL((k_march_line<Op, false>), dim3(grid), dim3(march::kBlock), 0, st, A, op, dirs, rest,
-                               ds_scale);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(march::kBlock), 0, st, A, op, dirs, rest, ds_scale);
+        };
+        if (f16 && rest) launch(k_march_line<Op, true, true>);
+        else if (f16) launch(k_march_line<Op, true, false>);
+        else if (rest) launch(k_march_line<Op, false, true>);
+        else launch(k_march_line<Op, false, false>);
         return hipGetLastError();
     };
     return small_a ? go(LineOpT<true, G>{}) : go(LineOpT<false, G>{});
